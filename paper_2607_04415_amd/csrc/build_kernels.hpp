@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "ordered_sum.hpp"
 
 namespace gorio {
 
@@ -56,34 +57,163 @@ __global__ __launch_bounds__(256) void pack_records(const uint8_t *vectors, uint
 }
 
 // ---- medoid -----------------------------------------------------------------
-// uint8: exact column sums (any order gives the same integers).
+// uint8: exact column sums (any order gives the same integers).  A block takes
+// kSumRows rows; thread t sums the dword column t % dw over every
+// (256 / dw)-th row, the block adds its partial sums in LDS and then once per
+// column in memory.  Bound by the one read of the rows; the first form (one
+// thread per byte column, 4,096 rows per block: 74 blocks at 300k rows, one
+// byte per load) took 787 us there.
+constexpr uint32_t kSumRows = 512;  // 512 * 255 fits 32 bits with room
 __global__ __launch_bounds__(256) void column_sums_u8(const uint8_t *x, uint32_t n, uint32_t D,
-                                                      uint32_t rows_per_block,
                                                       unsigned long long *sums) {
-  const uint32_t r0 = blockIdx.x * rows_per_block;
-  const uint32_t r1 = min(n, r0 + rows_per_block);
-  for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) {
-    unsigned long long s = 0;
-    for (uint32_t i = r0; i < r1; ++i) s += x[(uint64_t)i * D + d];
-    atomicAdd(&sums[d], s);
+  __shared__ uint32_t part[512];
+  for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) part[d] = 0;
+  __syncthreads();
+  const uint32_t dw = D / 4, groups = blockDim.x / dw;  // D <= 512: at least one group
+  const uint32_t g = threadIdx.x / dw, c = threadIdx.x % dw;
+  const uint32_t r0 = blockIdx.x * kSumRows, r1 = min(n, r0 + kSumRows);
+  if (g < groups) {
+    const uint32_t *w = reinterpret_cast<const uint32_t *>(x) + c;
+    uint32_t s[4] = {0, 0, 0, 0};
+#pragma unroll 8
+    for (uint32_t i = r0 + g; i < r1; i += groups) {
+      const uint32_t v = w[(uint64_t)i * dw];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) s[b] += (v >> (8 * b)) & 0xFFu;
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) atomicAdd(&part[4 * c + b], s[b]);
+  }
+  __syncthreads();
+  for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) atomicAdd(&sums[d], (unsigned long long)part[d]);
+}
+
+// float32: column sums in float64 in node order.  The order is part of the
+// entry rule, and a serial chain over n rows waits for memory and adder alike
+// (1M x 96: 65.4 ms with one thread per column and eight loads in flight), so
+// the runs of kSumRun rows are worked out side by side (ordered_sum.hpp): the
+// rows are read twice at memory speed, and the chain that is left has one step
+// per run (1M x 96: see launch_column_sums_f32).
+__global__ __launch_bounds__(256) void sum_outlines_f32(const float *x, uint32_t n, uint32_t D, uint32_t runs,
+                                                        RunOutline *out) {
+  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (uint64_t)runs * D) return;
+  const uint32_t c = (uint32_t)(t / D), d = (uint32_t)(t - (uint64_t)c * D);
+  const uint32_t r0 = c * kSumRun, rows = min(kSumRun, n - r0);
+  const float *p = x + (uint64_t)r0 * D + d;
+  RunOutline o = outline_start();
+#pragma unroll 16
+  for (uint32_t i = 0; i < rows; ++i) outline_add(o, (double)p[(uint64_t)i * D]);
+  out[t] = o;
+}
+
+// One block per column: the runs' start sums (plain prefix sums, kept in
+// place of the outlines' sums) and the largest magnitude a partial sum reaches.
+__global__ __launch_bounds__(256) void sum_starts_f32(RunOutline *runs_out, uint32_t D, uint32_t runs, double *most) {
+  __shared__ double part[256];
+  const uint32_t d = blockIdx.x, t = threadIdx.x;
+  const uint32_t each = (runs + 255) / 256, c0 = min(runs, t * each), c1 = min(runs, c0 + each);
+  double s = 0.0;
+  for (uint32_t c = c0; c < c1; ++c) s += runs_out[(uint64_t)c * D + d].sum;
+  part[t] = s;
+  __syncthreads();
+  if (t == 0) {
+    double a = 0.0;
+    for (int i = 0; i < 256; ++i) {
+      const double v = part[i];
+      part[i] = a;
+      a += v;
+    }
+  }
+  __syncthreads();
+  s = part[t];
+  __syncthreads();
+  double m = 0.0;
+  for (uint32_t c = c0; c < c1; ++c) {
+    RunOutline &o = runs_out[(uint64_t)c * D + d];
+    const double sum = o.sum, lo = fabs(s + o.lo), hi = fabs(s + o.hi);
+    o.sum = s;
+    // (after a NaN every run is open: its start is one)
+    m = m >= lo ? m : lo;
+    m = m >= hi ? m : hi;
+    s += sum;
+  }
+  part[t] = m;
+  __syncthreads();
+  if (t == 0) {
+    for (int i = 1; i < 256; ++i) m = m >= part[i] ? m : part[i];
+    most[d] = m;
   }
 }
 
-// float32: one thread per dimension sums in node order in float64.
-__global__ void column_sums_f32_ordered(const float *x, uint32_t n, uint32_t D, double *sums) {
-  const uint32_t d = blockIdx.x * blockDim.x + threadIdx.x;
-  if (d >= D) return;
-  double s = 0.0;
-  uint32_t i = 0;
-  for (; i + 8 <= n; i += 8) {
-    float v[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = x[(uint64_t)(i + t) * D + d];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) s = __dadd_rn(s, (double)v[t]);
+__global__ __launch_bounds__(256) void sum_amounts_f32(const float *x, uint32_t n, uint32_t D, uint32_t runs,
+                                                       const RunOutline *outl, const double *most, RunAmount *out) {
+  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (uint64_t)runs * D) return;
+  const uint32_t c = (uint32_t)(t / D), d = (uint32_t)(t - (uint64_t)c * D);
+  const uint32_t r0 = c * kSumRun, rows = min(kSumRun, n - r0);
+  const RunOutline o = outl[t];
+  RunAmount a = {__longlong_as_double(0x7FF8000000000000ll), 0.0};
+  double even, odd;
+  if (o.lo == 0.0 && o.hi == 0.0) {
+    // every partial sum 0: all terms are zeros
+    a = {0.0, 0.0};
+  } else if (run_stand_ins(o.sum, o.lo, o.hi, sum_margin(n, most[d]), even, odd)) {
+    const float *p = x + (uint64_t)r0 * D + d;
+    double s0 = even, s1 = odd;
+#pragma unroll 16
+    for (uint32_t i = 0; i < rows; ++i) {
+      const double v = (double)p[(uint64_t)i * D];
+      s0 = __dadd_rn(s0, v);
+      s1 = __dadd_rn(s1, v);
+    }
+    a = {__dsub_rn(s0, even), __dsub_rn(s1, odd)};
   }
-  for (; i < n; ++i) s = __dadd_rn(s, (double)x[(uint64_t)i * D + d]);
-  sums[d] = s;
+  out[t] = a;
+}
+
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(v), lane));
+}
+
+// One wave per column: 64 runs' amounts are read at once, one per lane, and
+// added one after another; an open run's rows likewise.
+__global__ __launch_bounds__(kWave) void sum_chain_f32(const float *x, uint32_t n, uint32_t D, uint32_t runs,
+                                                       const RunAmount *amounts, double *sums) {
+  const uint32_t d = blockIdx.x, l = lane_id();
+  double s = 0.0;
+  RunAmount next = {0.0, 0.0};
+  if (l < runs) next = amounts[(uint64_t)l * D + d];
+  for (uint32_t c0 = 0; c0 < runs; c0 += kWave) {
+    const RunAmount a = next;
+    const uint32_t cn = c0 + kWave + l;
+    if (cn < runs) next = amounts[(uint64_t)cn * D + d];
+    const uint64_t open = ballot(!(a.even == a.even));
+    const uint32_t m = min((uint32_t)kWave, runs - c0);
+    for (uint32_t j = 0; j < m; ++j) {
+      if (!((open >> j) & 1ull)) {
+        const double e = readlane_f64(a.even, (int)j), o = readlane_f64(a.odd, (int)j);
+        s = __dadd_rn(s, sum_is_odd(s) ? o : e);
+        continue;
+      }
+      const uint32_t r0 = (c0 + j) * kSumRun, rows = min(kSumRun, n - r0);
+      constexpr int kBlocks = kSumRun / kWave;
+      float v[kBlocks];
+#pragma unroll
+      for (int b = 0; b < kBlocks; ++b) {
+        const uint32_t i = b * kWave + l;
+        v[b] = i < rows ? x[(uint64_t)(r0 + i) * D + d] : 0.0f;
+      }
+#pragma unroll
+      for (int b = 0; b < kBlocks; ++b) {
+        const uint32_t cnt = rows > (uint32_t)b * kWave ? min((uint32_t)kWave, rows - b * kWave) : 0u;
+#pragma unroll 8
+        for (uint32_t i = 0; i < cnt; ++i)
+          s = __dadd_rn(s, (double)__uint_as_float(readlane(__float_as_uint(v[b]), (int)i)));
+      }
+    }
+  }
+  if (l == 0) sums[d] = s;
 }
 
 // key = (distance bits << 32) | id, minimised with one atomic per block.

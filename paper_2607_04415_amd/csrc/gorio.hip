@@ -193,18 +193,27 @@ extern "C" gorio_status gorio_build_index(gorio_dtype dtype, const void *vectors
 
   // entry node
   if (entry == UINT32_MAX) {
-    DevBuf sums;
+    DevBuf sums, outlines, amounts;
     HIP_OR_FAIL(sums.alloc(sizeof(double) * D));
     fill_u32<<<1, 256, 0, s>>>(sums.as<uint32_t>(), 2ull * D, 0u);
     if (dtype == GORIO_U8) {
-      const uint32_t rows = 4096;
-      column_sums_u8<<<grid_for(n, rows, 1 << 30), 256, 0, s>>>(
-          d_vec.as<uint8_t>(), (uint32_t)n, D, rows, sums.as<unsigned long long>());
+      column_sums_u8<<<grid_for(n, kSumRows, 1 << 30), 256, 0, s>>>(
+          d_vec.as<uint8_t>(), (uint32_t)n, D, sums.as<unsigned long long>());
       nearest_to_centroid_u8<<<grid_for(n, 256, 2048), 256, 0, s>>>(
           d_vec.as<uint8_t>(), (uint32_t)n, D, sums.as<unsigned long long>(), best);
     } else {
-      column_sums_f32_ordered<<<(D + 63) / 64, 64, 0, s>>>(d_vec.as<float>(), (uint32_t)n, D,
-                                                           sums.as<double>());
+      const uint32_t runs = (uint32_t)((n + kSumRun - 1) / kSumRun);
+      const uint64_t items = (uint64_t)runs * D;
+      HIP_OR_FAIL(outlines.alloc(items * sizeof(RunOutline)));
+      HIP_OR_FAIL(amounts.alloc(items * sizeof(RunAmount) + D * sizeof(double)));
+      double *most = reinterpret_cast<double *>(amounts.as<RunAmount>() + items);
+      const int grid = grid_for(items, 256, 1 << 30);
+      const float *x = d_vec.as<float>();
+      sum_outlines_f32<<<grid, 256, 0, s>>>(x, (uint32_t)n, D, runs, outlines.as<RunOutline>());
+      sum_starts_f32<<<D, 256, 0, s>>>(outlines.as<RunOutline>(), D, runs, most);
+      sum_amounts_f32<<<grid, 256, 0, s>>>(x, (uint32_t)n, D, runs, outlines.as<RunOutline>(), most,
+                                           amounts.as<RunAmount>());
+      sum_chain_f32<<<D, kWave, 0, s>>>(x, (uint32_t)n, D, runs, amounts.as<RunAmount>(), sums.as<double>());
       nearest_to_centroid_f32<<<grid_for(n, 256, 2048), 256, 0, s>>>(d_vec.as<float>(), (uint32_t)n, D,
                                                                     sums.as<double>(), best);
     }
