@@ -14,57 +14,14 @@
 
 #include <algorithm>
 #include <cstring>
-#include <thread>
 #include <vector>
 
 #include "../../include/gorio.h"
 #include "cluster.hpp"
+#include "cluster_kernels.hpp"
 
 namespace gorio {
 gorio_status fail(gorio_status st, const char *fmt, ...);
-
-// Nearest centroid of each vector: argmin_k (|c_k|^2 - 2 x . c_k), float32
-// arithmetic, d in order, ties to the smaller k.  One thread per vector;
-// every lane of a wave reads the same centroid element (a broadcast).  With
-// the dimension known at compile time (DC > 0) the vector is held in
-// registers and each centroid is read once per wave through scalar loads.
-template <typename T, int DC>
-__global__ __launch_bounds__(256) void nearest_centroid(const T *v, uint64_t count, uint32_t D, const float *c,
-                                                        const float *cc, uint32_t K, uint32_t *out) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const T *x = v + i * D;
-  float best = 0.0f;
-  uint32_t arg = 0;
-  if constexpr (DC > 0) {
-    float xr[DC];
-#pragma unroll
-    for (int d = 0; d < DC; ++d) xr[d] = (float)x[d];
-    for (uint32_t k = 0; k < K; ++k) {
-      const float *ck = c + (uint64_t)k * DC;
-      float dot = 0.0f;
-#pragma unroll
-      for (int d = 0; d < DC; ++d) dot += xr[d] * ck[d];
-      const float s = cc[k] - 2.0f * dot;
-      if (k == 0 || s < best) {
-        best = s;
-        arg = k;
-      }
-    }
-  } else {
-    for (uint32_t k = 0; k < K; ++k) {
-      const float *ck = c + (uint64_t)k * D;
-      float dot = 0.0f;
-      for (uint32_t d = 0; d < D; ++d) dot += (float)x[d] * ck[d];
-      const float s = cc[k] - 2.0f * dot;
-      if (k == 0 || s < best) {
-        best = s;
-        arg = k;
-      }
-    }
-  }
-  out[i] = arg;
-}
 
 template <typename T>
 hipError_t launch_nearest_centroid_t(const T *v, uint64_t count, uint32_t D, const float *c, const float *cc,
@@ -88,6 +45,62 @@ hipError_t launch_nearest_centroid(gorio_dtype dt, const void *v, uint64_t count
     return launch_nearest_centroid_t(static_cast<const uint8_t *>(v), count, D, c, cc, K, out, s);
   return launch_nearest_centroid_t(static_cast<const float *>(v), count, D, c, cc, K, out, s);
 }
+
+namespace {
+
+// Device memory of one gorio_cluster_order call.
+struct ClusterWork {
+  uint32_t Kp, DP;         // centroids and dimensions, padded for the matrix path
+  float *c;                // K x D
+  float *rows, *cols, *cc; // centroid_layouts' outputs
+  unsigned int *flags;     // [pairs, open vectors, largest norm's bits]
+  uint32_t *key, *alt, *pairs, *open;
+};
+
+// The matrix path takes whole batches: below these sizes (no wave for every
+// SIMD, or tiles mostly padding) the plain kernel is as fast, and its register
+// arrays end at 256 dimensions.
+bool matrix_path(uint64_t count, uint32_t D, uint32_t K) { return D <= 256 && K >= 32 && count >= 16384; }
+uint32_t padded_dims(uint32_t D) { return D <= 32 ? 32 : D <= 64 ? 64 : D <= 96 ? 96 : D <= 128 ? 128 : D <= 192 ? 192 : 256; }
+
+template <typename T, int DQ, int NT>
+void launch_matrix(const T *v, uint64_t n, uint32_t D, const ClusterWork &w, hipStream_t s) {
+  const unsigned grid = (unsigned)((n + 128 * NT - 1) / (128 * NT));
+  nearest_matrix<T, DQ, NT><<<grid, 256, 0, s>>>(v, n, D, w.rows, w.cc, w.Kp, w.flags + 2, w.key, w.alt, w.pairs,
+                                                 w.open, w.flags);
+}
+
+// w.key = nearest centroid of every vector.
+template <typename T>
+hipError_t assign(const T *v, uint64_t n, uint32_t D, uint32_t K, const ClusterWork &w, hipStream_t s) {
+  fill_words<<<1, 64, 0, s>>>(w.flags, 4, 0u);
+  centroid_layouts<<<(w.Kp + 63) / 64, 64, 0, s>>>(w.c, K, D, w.DP, w.Kp, w.rows, w.cols, w.cc, w.flags + 2);
+  if (!matrix_path(n, D, K)) return launch_nearest_centroid_t(v, n, D, w.c, w.cc, K, w.key, s);
+  switch (w.DP) {
+    case 32: launch_matrix<T, 4, 2>(v, n, D, w, s); break;
+    case 64: launch_matrix<T, 8, 2>(v, n, D, w, s); break;
+    case 96: launch_matrix<T, 12, 2>(v, n, D, w, s); break;
+    case 128: launch_matrix<T, 16, 2>(v, n, D, w, s); break;
+    case 192: launch_matrix<T, 24, 1>(v, n, D, w, s); break;
+    default: launch_matrix<T, 32, 1>(v, n, D, w, s); break;
+  }
+  nearest_of_pair<T><<<1024, 256, 0, s>>>(v, D, w.c, w.cc, w.pairs, w.flags, w.alt, w.key);
+  nearest_of_all<T><<<2048, kWave, 0, s>>>(v, D, w.cols, w.cc, K, w.Kp, w.open, w.flags + 1, w.key);
+  return hipGetLastError();
+}
+
+template <typename T>
+void launch_sums(const T *v, uint64_t n, uint32_t D, uint32_t K, const uint32_t *order, const uint32_t *start,
+                 double *sums, hipStream_t s) {
+  const dim3 grid(K, kMeanRanges);
+  auto threads = [](uint32_t units) { return std::min(256u, (units + 63) / 64 * 64); };
+  if (sizeof(T) == 1 && D % 4 == 0)
+    cluster_sums<T, sizeof(T) == 1 ? 4 : 1><<<grid, threads(D / 4), 0, s>>>(v, n, D, order, start, sums);
+  else
+    cluster_sums<T, 1><<<grid, threads(D), 0, s>>>(v, n, D, order, start, sums);
+}
+
+}  // namespace
 
 void centroid_norms(const float *c, uint32_t K, uint32_t D, float *cc) {
   for (uint32_t k = 0; k < K; ++k) {
@@ -138,83 +151,87 @@ extern "C" gorio_status gorio_cluster_order(gorio_dtype dtype, const void *vecto
   if (clusters == 0 || clusters > kMaxClusters || clusters > n)
     return fail(GORIO_EINVAL, "clusters=%u outside [1, min(n, %u)]", clusters, kMaxClusters);
   if (iterations > 64) return fail(GORIO_EINVAL, "iterations=%u above 64", iterations);
-  const uint32_t K = clusters;
+  const uint32_t K = clusters, N = (uint32_t)n;
   const size_t eb = dtype == GORIO_U8 ? 1 : 4;
   StreamGuard sg;
   HIP_OR_FAIL(hipStreamCreateWithFlags(&sg.s, hipStreamNonBlocking));
-  Buf d_v, d_c, d_cc, d_key;
-  HIP_OR_FAIL(d_v.alloc(n * D * eb));
-  HIP_OR_FAIL(d_c.alloc((size_t)K * D * 4));
-  HIP_OR_FAIL(d_cc.alloc((size_t)K * 4));
-  HIP_OR_FAIL(d_key.alloc(n * 4));
-  HIP_OR_FAIL(hipMemcpyAsync(d_v.p, vectors, n * D * eb, hipMemcpyHostToDevice, sg.s));
+  hipStream_t s = sg.s;
+  ClusterWork w;
+  w.Kp = (K + 31) / 32 * 32;
+  w.DP = D <= 256 ? padded_dims(D) : D;
+  // tiles of the counting sort: 2,048 nodes (32 steps of a wave), more when
+  // many clusters would make the table of counts large
+  uint32_t tile = 2048;
+  while ((uint64_t)((N + tile - 1) / tile) * K > (1ull << 26) && tile < (1u << 30)) tile *= 2;
+  const uint32_t tiles = (N + tile - 1) / tile;
+  uint32_t key_bits = 0;
+  while ((1ull << key_bits) < K) ++key_bits;
+
+  size_t bytes = 0;
+  auto take = [&](size_t b) {
+    const size_t at = bytes;
+    bytes += (b + 255) & ~(size_t)255;
+    return at;
+  };
+  const size_t o_v = take(n * D * eb), o_c = take((size_t)K * D * 4), o_rows = take((size_t)w.Kp * w.DP * 4),
+               o_cols = take((size_t)w.Kp * D * 4), o_cc = take((size_t)w.Kp * 4), o_flags = take(16),
+               o_key = take(n * 4), o_alt = take(n * 4), o_pairs = take(n * 4), o_open = take(n * 4),
+               o_slot = take(n * 4), o_hist = take((size_t)tiles * K * 4), o_total = take((size_t)K * 4),
+               o_start = take((size_t)(K + 1) * 4),
+               o_sums = take(iterations ? (size_t)kMeanRanges * K * D * sizeof(double) : 0);
+  Buf work;
+  HIP_OR_FAIL(work.alloc(bytes));
+  uint8_t *base = static_cast<uint8_t *>(work.p);
+  auto words = [&](size_t at) { return reinterpret_cast<uint32_t *>(base + at); };
+  auto floats = [&](size_t at) { return reinterpret_cast<float *>(base + at); };
+  w.c = floats(o_c);
+  w.rows = floats(o_rows);
+  w.cols = floats(o_cols);
+  w.cc = floats(o_cc);
+  w.flags = words(o_flags);
+  w.key = words(o_key);
+  w.alt = words(o_alt);
+  w.pairs = words(o_pairs);
+  w.open = words(o_open);
+  uint32_t *slot = words(o_slot), *order = w.alt, *rank = w.pairs;  // the lists are done with by then
+  uint32_t *hist = words(o_hist), *total = words(o_total), *start = words(o_start);
+  double *sums = reinterpret_cast<double *>(base + o_sums);
+  const uint8_t *v8 = base + o_v;
+  const float *vf = floats(o_v);
+  HIP_OR_FAIL(hipMemcpyAsync(base + o_v, vectors, n * D * eb, hipMemcpyHostToDevice, s));
 
   // initial centroids: the vectors of nodes i * n / K (distinct ids)
-  std::vector<float> c((size_t)K * D), cc(K);
-  auto elem = [&](uint64_t i, uint32_t d) -> double {
-    return dtype == GORIO_U8 ? (double)static_cast<const uint8_t *>(vectors)[i * D + d]
-                             : (double)static_cast<const float *>(vectors)[i * D + d];
-  };
+  std::vector<float> c((size_t)K * D);
   for (uint32_t k = 0; k < K; ++k) {
     const uint64_t i = (uint64_t)k * n / K;
-    for (uint32_t d = 0; d < D; ++d) c[(size_t)k * D + d] = (float)elem(i, d);
+    for (uint32_t d = 0; d < D; ++d)
+      c[(size_t)k * D + d] = dtype == GORIO_U8 ? (float)static_cast<const uint8_t *>(vectors)[i * D + d]
+                                               : static_cast<const float *>(vectors)[i * D + d];
   }
-  std::vector<uint32_t> key(n);
-  // Lloyd updates on the host: 16 threads sum fixed node ranges in float64,
-  // then the partial sums are added in range order (the same result on any
-  // machine)
-  const uint32_t nt = 16;
-  std::vector<std::vector<double>> sums(nt, std::vector<double>((size_t)K * D));
-  std::vector<std::vector<uint64_t>> cnts(nt, std::vector<uint64_t>(K));
-  auto accumulate = [&](uint32_t t) {
-    std::vector<double> &sum = sums[t];
-    std::vector<uint64_t> &cnt = cnts[t];
-    std::fill(sum.begin(), sum.end(), 0.0);
-    std::fill(cnt.begin(), cnt.end(), 0);
-    const uint64_t i0 = n * t / nt, i1 = n * (t + 1) / nt;
-    for (uint64_t i = i0; i < i1; ++i) {
-      const uint32_t k = key[i];
-      ++cnt[k];
-      double *sk = sum.data() + (size_t)k * D;
-      if (dtype == GORIO_U8) {
-        const uint8_t *x = static_cast<const uint8_t *>(vectors) + i * D;
-        for (uint32_t d = 0; d < D; ++d) sk[d] += x[d];
-      } else {
-        const float *x = static_cast<const float *>(vectors) + i * D;
-        for (uint32_t d = 0; d < D; ++d) sk[d] += x[d];
-      }
-    }
-  };
+  HIP_OR_FAIL(hipMemcpyAsync(w.c, c.data(), c.size() * 4, hipMemcpyHostToDevice, s));
+
+  // Lloyd iterations, then the placement: cluster by cluster, id order inside
+  // a cluster.  Nothing returns to the host in between.
   for (uint32_t it = 0;; ++it) {
-    centroid_norms(c.data(), K, D, cc.data());
-    HIP_OR_FAIL(hipMemcpyAsync(d_c.p, c.data(), c.size() * 4, hipMemcpyHostToDevice, sg.s));
-    HIP_OR_FAIL(hipMemcpyAsync(d_cc.p, cc.data(), cc.size() * 4, hipMemcpyHostToDevice, sg.s));
-    HIP_OR_FAIL(launch_nearest_centroid(dtype, d_v.p, n, D, static_cast<float *>(d_c.p),
-                                        static_cast<float *>(d_cc.p), K, static_cast<uint32_t *>(d_key.p), sg.s));
-    HIP_OR_FAIL(hipMemcpyAsync(key.data(), d_key.p, n * 4, hipMemcpyDeviceToHost, sg.s));
-    HIP_OR_FAIL(hipStreamSynchronize(sg.s));
+    HIP_OR_FAIL(dtype == GORIO_U8 ? assign(v8, n, D, K, w, s) : assign(vf, n, D, K, w, s));
+    const uint64_t cells = (uint64_t)tiles * K;
+    fill_words<<<(unsigned)std::min<uint64_t>(4096, (cells + 255) / 256), 256, 0, s>>>(hist, cells, 0u);
+    tile_ranks<<<tiles, kWave, 0, s>>>(w.key, N, K, key_bits, tile, hist, rank);
+    tile_prefix<<<(K + 63) / 64, 64, 0, s>>>(hist, tiles, K, total);
+    cluster_starts<<<1, 1024, 0, s>>>(total, K, start);
+    cluster_slots<<<(N + 255) / 256, 256, 0, s>>>(w.key, rank, hist, start, N, K, tile, slot, order);
+    HIP_OR_FAIL(hipGetLastError());
     if (it == iterations) break;
     // each centroid becomes the mean of its members (an empty cluster keeps
     // its centroid)
-    std::vector<std::thread> pool;
-    for (uint32_t t = 1; t < nt; ++t) pool.emplace_back(accumulate, t);
-    accumulate(0);
-    for (auto &th : pool) th.join();
-    for (uint32_t k = 0; k < K; ++k) {
-      uint64_t cnt = 0;
-      for (uint32_t t = 0; t < nt; ++t) cnt += cnts[t][k];
-      if (!cnt) continue;
-      for (uint32_t d = 0; d < D; ++d) {
-        double sd = 0.0;
-        for (uint32_t t = 0; t < nt; ++t) sd += sums[t][(size_t)k * D + d];
-        c[(size_t)k * D + d] = (float)(sd / (double)cnt);
-      }
-    }
+    if (dtype == GORIO_U8) launch_sums(v8, n, D, K, order, start, sums, s);
+    else launch_sums(vf, n, D, K, order, start, sums, s);
+    cluster_means<<<(unsigned)(((uint64_t)K * D + 255) / 256), 256, 0, s>>>(sums, start, K, D, w.c);
+    HIP_OR_FAIL(hipGetLastError());
   }
-  // cluster by cluster, id order inside a cluster
-  std::vector<uint32_t> order(n);
-  order_by_key(key.data(), n, K, order.data());
-  for (uint64_t s = 0; s < n; ++s) node_to_slot[order[s]] = (uint32_t)s;
+  HIP_OR_FAIL(hipMemcpyAsync(c.data(), w.c, c.size() * 4, hipMemcpyDeviceToHost, s));
+  HIP_OR_FAIL(hipMemcpyAsync(node_to_slot, slot, n * 4, hipMemcpyDeviceToHost, s));
+  HIP_OR_FAIL(hipStreamSynchronize(s));
   memcpy(centroids, c.data(), c.size() * 4);
   return GORIO_OK;
 }
