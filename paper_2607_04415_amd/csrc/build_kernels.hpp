@@ -103,13 +103,14 @@ __global__ __launch_bounds__(256) void sum_outlines_f32(const float *x, uint32_t
   const float *p = x + (uint64_t)r0 * D + d;
   RunOutline o = outline_start();
 #pragma unroll 16
-  for (uint32_t i = 0; i < rows; ++i) outline_add(o, (double)p[(uint64_t)i * D]);
+  for (uint32_t i = 0; i < rows; ++i) outline_add(o, p[(uint64_t)i * D]);
   out[t] = o;
 }
 
 // One block per column: the runs' start sums (plain prefix sums, kept in
-// place of the outlines' sums) and the largest magnitude a partial sum reaches.
-__global__ __launch_bounds__(256) void sum_starts_f32(RunOutline *runs_out, uint32_t D, uint32_t runs, double *most) {
+// place of the outlines' sums, which move to `plain`) and the largest magnitude a partial sum reaches.
+__global__ __launch_bounds__(256) void sum_starts_f32(RunOutline *runs_out, double *plain, uint32_t D, uint32_t runs,
+                                                      double *most) {
   __shared__ double part[256];
   const uint32_t d = blockIdx.x, t = threadIdx.x;
   const uint32_t each = (runs + 255) / 256, c0 = min(runs, t * each), c1 = min(runs, c0 + each);
@@ -133,6 +134,7 @@ __global__ __launch_bounds__(256) void sum_starts_f32(RunOutline *runs_out, uint
     RunOutline &o = runs_out[(uint64_t)c * D + d];
     const double sum = o.sum, lo = fabs(s + o.lo), hi = fabs(s + o.hi);
     o.sum = s;
+    plain[(uint64_t)c * D + d] = sum;
     // (after a NaN every run is open: its start is one)
     m = m >= lo ? m : lo;
     m = m >= hi ? m : hi;
@@ -147,18 +149,21 @@ __global__ __launch_bounds__(256) void sum_starts_f32(RunOutline *runs_out, uint
 }
 
 __global__ __launch_bounds__(256) void sum_amounts_f32(const float *x, uint32_t n, uint32_t D, uint32_t runs,
-                                                       const RunOutline *outl, const double *most, RunAmount *out) {
+                                                       const RunOutline *outl, const double *plain, const double *most,
+                                                       RunAmount *out) {
   const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (uint64_t)runs * D) return;
   const uint32_t c = (uint32_t)(t / D), d = (uint32_t)(t - (uint64_t)c * D);
   const uint32_t r0 = c * kSumRun, rows = min(kSumRun, n - r0);
   const RunOutline o = outl[t];
-  RunAmount a = {__longlong_as_double(0x7FF8000000000000ll), 0.0};
+  const double margin = sum_margin(n, most[d]);
+  RunAmount a = run_open(o, margin);
+  a.odd = plain[t];
   double even, odd;
   if (o.lo == 0.0 && o.hi == 0.0) {
     // every partial sum 0: all terms are zeros
     a = {0.0, 0.0};
-  } else if (run_stand_ins(o.sum, o.lo, o.hi, sum_margin(n, most[d]), even, odd)) {
+  } else if (run_stand_ins(o.sum, o.lo, o.hi, margin, even, odd)) {
     const float *p = x + (uint64_t)r0 * D + d;
     double s0 = even, s1 = odd;
 #pragma unroll 16
@@ -196,6 +201,10 @@ __global__ __launch_bounds__(kWave) void sum_chain_f32(const float *x, uint32_t 
         s = __dadd_rn(s, sum_is_odd(s) ? o : e);
         continue;
       }
+      if (run_is_exact(s, readlane_f64(a.even, (int)j))) {
+        s = __dadd_rn(s, readlane_f64(a.odd, (int)j));
+        continue;
+      }
       const uint32_t r0 = (c0 + j) * kSumRun, rows = min(kSumRun, n - r0);
       constexpr int kBlocks = kSumRun / kWave;
       float v[kBlocks];
@@ -207,7 +216,6 @@ __global__ __launch_bounds__(kWave) void sum_chain_f32(const float *x, uint32_t 
 #pragma unroll
       for (int b = 0; b < kBlocks; ++b) {
         const uint32_t cnt = rows > (uint32_t)b * kWave ? min((uint32_t)kWave, rows - b * kWave) : 0u;
-#pragma unroll 8
         for (uint32_t i = 0; i < cnt; ++i)
           s = __dadd_rn(s, (double)__uint_as_float(readlane(__float_as_uint(v[b]), (int)i)));
       }

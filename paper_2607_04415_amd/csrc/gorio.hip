@@ -205,13 +205,13 @@ extern "C" gorio_status gorio_build_index(gorio_dtype dtype, const void *vectors
       const uint32_t runs = (uint32_t)((n + kSumRun - 1) / kSumRun);
       const uint64_t items = (uint64_t)runs * D;
       HIP_OR_FAIL(outlines.alloc(items * sizeof(RunOutline)));
-      HIP_OR_FAIL(amounts.alloc(items * sizeof(RunAmount) + D * sizeof(double)));
-      double *most = reinterpret_cast<double *>(amounts.as<RunAmount>() + items);
+      HIP_OR_FAIL(amounts.alloc(items * (sizeof(RunAmount) + sizeof(double)) + D * sizeof(double)));
+      double *plain = reinterpret_cast<double *>(amounts.as<RunAmount>() + items), *most = plain + items;
       const int grid = grid_for(items, 256, 1 << 30);
       const float *x = d_vec.as<float>();
       sum_outlines_f32<<<grid, 256, 0, s>>>(x, (uint32_t)n, D, runs, outlines.as<RunOutline>());
-      sum_starts_f32<<<D, 256, 0, s>>>(outlines.as<RunOutline>(), D, runs, most);
-      sum_amounts_f32<<<grid, 256, 0, s>>>(x, (uint32_t)n, D, runs, outlines.as<RunOutline>(), most,
+      sum_starts_f32<<<D, 256, 0, s>>>(outlines.as<RunOutline>(), plain, D, runs, most);
+      sum_amounts_f32<<<grid, 256, 0, s>>>(x, (uint32_t)n, D, runs, outlines.as<RunOutline>(), plain, most,
                                            amounts.as<RunAmount>());
       sum_chain_f32<<<D, kWave, 0, s>>>(x, (uint32_t)n, D, runs, amounts.as<RunAmount>(), sums.as<double>());
       nearest_to_centroid_f32<<<grid_for(n, 256, 2048), 256, 0, s>>>(d_vec.as<float>(), (uint32_t)n, D,

@@ -13,14 +13,16 @@
 //   outline  each run's plain sum and the range of its partial sums;
 //   amounts  from the prefix sums of the outline: where s stays in one binade
 //            during the run, with a margin above all rounding errors, the two
-//            amounts; else the run is marked open;
-//   chain    run by run, s plus the amount of its parity; the terms of an
-//            open run one after another.
+//            amounts; else the run is marked open, with its plain sum where that
+//            may serve;
+//   chain    run by run, s plus the amount of its parity; an open run's plain
+//            sum, or its terms one after another.
 //
 // Plain functions, so that the same lines run on the CPU in a test.
 #pragma once
 
 #include <math.h>
+#include <limits.h>
 #include <stdint.h>
 #include <string.h>
 
@@ -34,24 +36,41 @@ namespace gorio {
 
 constexpr uint32_t kSumRun = 256;  // terms per run
 
-// A run's plain sum and the least and greatest of its partial sums (that of
-// no terms, 0, included).
+// A run's plain sum, the least and greatest of its partial sums (that of no
+// terms, 0, included) and the exponent of the lowest bit set in any term.
 struct RunOutline {
   double sum, lo, hi;
+  int low;
 };
 
-// What a run adds to a sum whose multiple of the spacing is even / odd.
-// even = NaN marks an open run.
+// What a run adds to a sum whose multiple of the spacing is even / odd.  An
+// open run has a NaN in `even`; its payload is 0, or kUnitBias + the exponent
+// of a unit that divides all its terms and in which its partial sums need no
+// more than 53 bits, and then `odd` is the run's plain sum.
 struct RunAmount {
   double even, odd;
 };
+constexpr int kUnitBias = 2048;
 
-GORIO_HD RunOutline outline_start() { return {0.0, 0.0, 0.0}; }
-GORIO_HD void outline_add(RunOutline &o, double x) {
-  o.sum += x;
+// Exponent of a float's lowest set bit (INT_MAX: none).
+GORIO_HD int lowest_bit(float x) {
+  uint32_t b;
+  memcpy(&b, &x, 4);
+  uint32_t m = b & 0x7FFFFFu;
+  int e = (int)((b >> 23) & 0xFFu);
+  if (e) m |= 0x800000u;
+  else e = 1;
+  return m ? e - 150 + __builtin_ctz(m) : INT_MAX;
+}
+
+GORIO_HD RunOutline outline_start() { return {0.0, 0.0, 0.0, INT_MAX}; }
+GORIO_HD void outline_add(RunOutline &o, float x) {
+  o.sum += (double)x;
   // a NaN partial sum stays in lo and hi
   o.lo = o.lo < o.sum ? o.lo : o.sum;
   o.hi = o.hi > o.sum ? o.hi : o.sum;
+  const int e = lowest_bit(x);
+  o.low = e < o.low ? e : o.low;
 }
 
 GORIO_HD double sum_bits_as_double(uint64_t b) {
@@ -89,6 +108,28 @@ GORIO_HD bool run_stand_ins(double start, double lo, double hi, double margin, d
   even = sum_bits_as_double(sum_double_bits(start) & ~1ull);
   odd = sum_bits_as_double(sum_double_bits(start) | 1ull);
   return true;
+}
+
+// 2^e for e within the normal range.
+GORIO_HD double sum_pow2(int e) { return sum_bits_as_double((uint64_t)(e + 1023) << 52); }
+
+// The mark of an open run (see RunAmount): with far < 2^e the bound of its
+// partial sums, whole multiples of 2^(e - 52) are added without rounding.
+GORIO_HD RunAmount run_open(const RunOutline &o, double margin) {
+  const uint64_t nan = 0x7FF8000000000000ull;
+  const double far = fmax(fabs(o.sum + o.lo), fabs(o.sum + o.hi)) + margin;
+  if (far < 0x1p400) {
+    const int unit = (int)(sum_double_bits(far) >> 52) - 1023 + 1 - 52;
+    if (unit > -1000 && o.low >= unit) return {sum_bits_as_double(nan | (uint64_t)(unit + kUnitBias)), 0.0};
+  }
+  return {sum_bits_as_double(nan), 0.0};
+}
+// Whether an open run's plain sum can be added to s.
+GORIO_HD bool run_is_exact(double s, double mark) {
+  const int p = (int)(sum_double_bits(mark) & 0xFFFFull);
+  if (p == 0) return false;
+  const double t = s * sum_pow2(kUnitBias - p);  // s in units, below 2^53
+  return rint(t) == t;
 }
 
 // Whether a sum is an odd multiple of its binade's spacing.

@@ -43,15 +43,17 @@ int main(int argc, char **argv) {
   const size_t runs = (n + kSumRun - 1) / kSumRun;
   auto end_of = [&](size_t c) { return (c + 1) * kSumRun < n ? (c + 1) * kSumRun : n; };
   std::vector<RunOutline> o(runs);
+  std::vector<double> sum(runs);
   for (size_t c = 0; c < runs; ++c) {
     o[c] = outline_start();
-    for (size_t i = c * kSumRun; i < end_of(c); ++i) outline_add(o[c], (double)x[i]);
+    for (size_t i = c * kSumRun; i < end_of(c); ++i) outline_add(o[c], x[i]);
   }
   double start = 0.0, most = 0.0;
   for (size_t c = 0; c < runs; ++c) {
     const double s = o[c].sum, lo = fabs(start + o[c].lo), hi = fabs(start + o[c].hi);
     most = most >= lo ? most : lo;
     most = most >= hi ? most : hi;
+    sum[c] = s;
     o[c].sum = start;
     start += s;
   }
@@ -67,6 +69,8 @@ int main(int argc, char **argv) {
         s1 += (double)x[i];
       }
       s += sum_is_odd(s) ? s1 - odd : s0 - even;
+    } else if (run_is_exact(s, run_open(o[c], sum_margin(n, most)).even)) {
+      s += sum[c];
     } else {
       ++open;
       for (size_t i = c * kSumRun; i < end_of(c); ++i) s += (double)x[i];

@@ -75,6 +75,8 @@ def data(kind, n, D, seed):
     ("f32", 3, 5, 3, 1),
 ])
 def test_cluster_order_is_the_stated_rule(kind, n, D, K, iterations):
+    import torch
+    assert torch.cuda.is_available()   # before the library: both then share one HIP runtime
     import paper_2607_04415_amd as g
     x = data(kind, n, D, n + D)
     n2s, c = g.cluster_order(x, K, iterations)

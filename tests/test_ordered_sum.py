@@ -30,7 +30,7 @@ def test_runs_equal_the_plain_loop(harness, kind, n):
         out = subprocess.run([str(harness), kind, str(n), str(seed)], capture_output=True, text=True, check=True).stdout
         f = out.split()
         assert f[3] == "1", out
-        if n == 300_000 and kind in ("drift", "fall", "whole"):
+        if n == 300_000 and kind in ("drift", "walk", "fall", "whole", "flip"):
             assert int(f[1]) < 100, out   # few of the 1,172 runs are summed term by term
 
 
@@ -38,6 +38,8 @@ def test_runs_equal_the_plain_loop(harness, kind, n):
 @pytest.mark.parametrize("n,D,kind", [(1, 1, "drift"), (256, 3, "walk"), (257, 96, "drift"), (20_000, 1, "drift"),
                                       (20_000, 1, "flip"), (30_001, 65, "walk"), (30_001, 1, "whole")])
 def test_entry_is_the_oracles(n, D, kind):
+    import torch
+    assert torch.cuda.is_available()   # before the library: both then share one HIP runtime
     import paper_2607_04415_amd as g
     from oracle import load
     rng = np.random.default_rng(n + D)
