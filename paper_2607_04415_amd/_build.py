@@ -40,7 +40,7 @@ def build(verbose: bool = False, extra: list[str] | None = None, jobs: int | Non
         return obj
 
     srcs = sources()
-    jobs = jobs or min(len(srcs), max(1, (os.cpu_count() or 2) // 2))
+    jobs = jobs or min(len(srcs), os.cpu_count() or 2)
     with ThreadPoolExecutor(jobs) as ex:
         objs = list(ex.map(compile_one, srcs))
     tmp = LIB.with_name(LIB.name + f".{tag}.tmp")

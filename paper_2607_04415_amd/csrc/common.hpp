@@ -12,7 +12,9 @@ namespace gorio {
 constexpr uint32_t kNoEdge = 0xFFFFFFFFu;
 constexpr uint32_t kHtEmpty = 0xFFFFFFFFu;
 constexpr int kCandCap = 256;  // candidate ids gathered per beam group
-constexpr int kMaxW = 256;
+// Bytes past the page array that its allocation holds: a ragged float32 row's
+// last 16-byte block may reach 12 bytes past the row.
+constexpr uint64_t kPageSlack = 16;
 
 // floor(x / d) for x < 2^31 with one 64-bit multiply:  m = ceil(2^(31+s) / d),
 // s = ceil(log2 d), q = (x * m) >> (31 + s)  (Granlund & Montgomery, PLDI 1994).
@@ -271,9 +273,12 @@ struct VisitedLds16 {
   static constexpr int kHashBits = kHomeBits + 14;
   static constexpr uint32_t kMaxId = 1u << (kHashBits < 24 ? kHashBits : 24);  // ids must be below this
 
+  // By a block of T waves.
+  template <int T = 1>
   __device__ __forceinline__ static void clear(uint32_t *t) {
     uint4 *t4 = reinterpret_cast<uint4 *>(t);
-    for (uint32_t i = lane_id(); i < kBuckets; i += kWave) t4[i] = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t first = T == 1 ? lane_id() : threadIdx.x;
+    for (uint32_t i = first; i < kBuckets; i += T * kWave) t4[i] = make_uint4(0u, 0u, 0u, 0u);
   }
 
   __device__ __forceinline__ static bool test_and_set(uint32_t *t, uint32_t id, bool may_store,
@@ -302,75 +307,104 @@ struct VisitedLds16 {
     return (m & 0xFFFFu) == 0 || (m >> 16) == 0;
   }
 
-  // Same contract as VisitedLds::test_and_set_n (ids below kMaxId).
+  // A call's state between its steps: N ids per lane.
   template <int N>
-  __device__ __forceinline__ static void test_and_set_n(uint32_t *t, const uint32_t (&ids)[N],
-                                                        const bool (&valid)[N], bool may_store,
-                                                        bool (&isnew)[N], bool (&recorded)[N]) {
-    const uint4 *t4 = reinterpret_cast<const uint4 *>(t);
-    uint16_t *t16 = reinterpret_cast<uint16_t *>(t);
+  struct Probe {
     uint32_t bk[N], e[N], slot[N];
-    bool claim[N], won[N], over[N];
+    bool claim[N], won[N], fresh[N];  // fresh: new, but nowhere to record it
+  };
+
+  // Step 1: both buckets of every id, and what to do about it.
+  template <int N>
+  __device__ __forceinline__ static void look(const uint32_t *t, const uint32_t (&ids)[N], const bool (&valid)[N],
+                                              bool may_store, Probe<N> &p) {
+    const uint4 *t4 = reinterpret_cast<const uint4 *>(t);
     uint4 v0[N], v1[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       // v_mul_u32_u24 reads the low 24 bits of each operand: exact for ids
       // below 2^24; an invalid lane's id only picks some bucket to read
       const uint32_t h = mul_u24(ids[i], 0x9E3779B1u & 0xFFFFFFu) & ((1u << kHashBits) - 1);
-      bk[i] = h >> 14;
-      e[i] = 1u + (h & 0x3FFFu);
-      v0[i] = t4[bk[i]];
-      v1[i] = t4[(bk[i] + 1) & (kBuckets - 1)];
+      p.bk[i] = h >> 14;
+      p.e[i] = 1u + (h & 0x3FFFu);
+      v0[i] = t4[p.bk[i]];
+      v1[i] = t4[(p.bk[i] + 1) & (kBuckets - 1)];
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const bool hit0 = holds(v0[i], e[i], kSlots);
-      const bool hit1 = holds(v1[i], e[i] + (1u << 14), kSlots);
+      const bool hit0 = holds(v0[i], p.e[i], kSlots);
+      const bool hit1 = holds(v1[i], p.e[i] + (1u << 14), kSlots);
       const bool full0 = (v0[i].w >> 16) >= kSlots, full1 = (v1[i].w >> 16) >= kSlots;
       // present: in home, or in the next bucket when home was full
       const bool present = hit0 || (full0 && hit1);
       const bool absent = valid[i] && !present;
       const bool lost = absent && full0 && full1;          // nowhere to record it
-      claim[i] = absent && !lost && may_store;
-      isnew[i] = absent && (lost || !may_store);
-      recorded[i] = false;
+      p.claim[i] = absent && !lost && may_store;
+      p.fresh[i] = absent && (lost || !may_store);
       // claim in home when it had room, else in the next bucket
       const uint32_t d = full0 ? 1u : 0u;
-      bk[i] = (bk[i] + d) & (kBuckets - 1);
-      e[i] += d << 14;
+      p.bk[i] = (p.bk[i] + d) & (kBuckets - 1);
+      p.e[i] += d << 14;
     }
-    asm volatile("" ::: "memory");  // the claims follow the bucket reads
+  }
+
+  // Step 2: take a slot of the bucket and write the entry.
+  template <int N>
+  __device__ __forceinline__ static void claim(uint32_t *t, Probe<N> &p) {
+    uint16_t *t16 = reinterpret_cast<uint16_t *>(t);
     uint32_t old[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       old[i] = 0;
-      if (claim[i]) old[i] = atomicAdd(&t[bk[i] * 4 + 3], 0x10000u);
+      if (p.claim[i]) old[i] = atomicAdd(&t[p.bk[i] * 4 + 3], 0x10000u);
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      slot[i] = old[i] >> 16;
-      won[i] = claim[i] && slot[i] < kSlots;
-      over[i] = claim[i] && slot[i] >= kSlots;              // lanes filled the bucket first
-      if (won[i]) t16[bk[i] * 8 + slot[i]] = (uint16_t)e[i];
+      p.slot[i] = old[i] >> 16;
+      p.won[i] = p.claim[i] && p.slot[i] < kSlots;          // else other lanes filled the bucket first
+      if (p.won[i]) t16[p.bk[i] * 8 + p.slot[i]] = (uint16_t)p.e[i];
     }
-    // LDS operations of one wave complete in order; keep the compiler from
-    // moving the read-back above the 16-bit stores
-    asm volatile("" ::: "memory");
+  }
+
+  // Step 3: read the bucket back.
+  template <int N>
+  __device__ __forceinline__ static void settle(const uint32_t *t, const Probe<N> &p, bool (&isnew)[N],
+                                                bool (&recorded)[N]) {
+    const uint4 *t4 = reinterpret_cast<const uint4 *>(t);
     bool any = false;
 #pragma unroll
-    for (int i = 0; i < N; ++i) any |= claim[i];
+    for (int i = 0; i < N; ++i) {
+      isnew[i] = p.fresh[i];
+      recorded[i] = false;
+      any |= p.claim[i];
+    }
     if (ballot(any) == 0) return;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      if (ballot(claim[i]) == 0) continue;
-      const uint4 v = t4[bk[i]];
+      if (ballot(p.claim[i]) == 0) continue;
+      const uint4 v = t4[p.bk[i]];
       // a lower slot holding the same entry belongs to another lane with this
       // id; a lane that found the bucket full keeps its id only if no lane
       // recorded it there
-      const bool dup = holds(v, e[i], won[i] ? slot[i] : kSlots);
-      isnew[i] = isnew[i] || (claim[i] && !dup);
-      recorded[i] = won[i] && !dup;
+      const bool dup = holds(v, p.e[i], p.won[i] ? p.slot[i] : kSlots);
+      isnew[i] = isnew[i] || (p.claim[i] && !dup);
+      recorded[i] = p.won[i] && !dup;
     }
+  }
+
+  // Same contract as VisitedLds::test_and_set_n (ids below kMaxId).
+  template <int N>
+  __device__ __forceinline__ static void test_and_set_n(uint32_t *t, const uint32_t (&ids)[N],
+                                                        const bool (&valid)[N], bool may_store,
+                                                        bool (&isnew)[N], bool (&recorded)[N]) {
+    Probe<N> p;
+    look(t, ids, valid, may_store, p);
+    asm volatile("" ::: "memory");  // the claims follow the bucket reads
+    claim(t, p);
+    // LDS operations of one wave complete in order; keep the compiler from
+    // moving the read-back above the 16-bit stores
+    asm volatile("" ::: "memory");
+    settle(t, p, isnew, recorded);
   }
 };
 

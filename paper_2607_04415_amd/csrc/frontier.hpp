@@ -124,26 +124,37 @@ __device__ __forceinline__ void merge_dedupe(uint64_t (&F)[KPL], uint64_t c_desc
 // chunks: 6, 12, 32 -> 0.848, 0.836, 0.846 ms per 10k-query launch).
 constexpr uint32_t kInsertMax = 12;
 
-// Sort-and-merge path for a one-register frontier, kept out of line: it is
-// rare after the first iterations, and one copy keeps the kernel small.
-static __device__ __noinline__ uint64_t sort_merge_1(uint64_t f, uint64_t key, bool forgot) {
-  uint64_t F[1] = {f};
+// Sort-and-merge path.  It is rare after the first iterations; kernels with
+// many merge sites call one copy (sort_merge_call), those that keep more
+// registers in flight across it than a call preserves have it inline.
+template <int KPL>
+struct FrontierRegs {
+  uint64_t f[KPL];
+};
+template <int KPL>
+static __device__ __forceinline__ FrontierRegs<KPL> sort_merge(FrontierRegs<KPL> x, uint64_t key, bool forgot) {
   uint64_t cc[1] = {key};
   bitonic_sort<1, true>(cc);
   if (!forgot) {
-    F[0] = min64(F[0], cc[0]);
-    bitonic_merge_up<1>(F);
+    // no node can repeat: the P smallest of F and C are min(F, C reversed)
+    x.f[KPL - 1] = min64(x.f[KPL - 1], cc[0]);
+    bitonic_merge_up<KPL>(x.f);
   } else {
-    merge_dedupe<1>(F, cc[0]);
+    merge_dedupe<KPL>(x.f, cc[0]);
   }
-  return F[0];
+  return x;
+}
+
+template <int KPL>
+static __device__ __noinline__ FrontierRegs<KPL> sort_merge_call(FrontierRegs<KPL> x, uint64_t key, bool forgot) {
+  return sort_merge<KPL>(x, key, forgot);
 }
 
 // Merge one key per lane (kInfKey = none) into F: keys at or above F's L-th
 // key cannot enter; a few survivors are inserted by rank, more are sorted
 // and bitonic-merged (with dedupe once the visited filter has forgotten a
 // node).  Slots past L are cleared.
-template <int KPL>
+template <int KPL, bool CALL = true>
 __device__ __forceinline__ void merge_keys(uint64_t (&F)[KPL], uint64_t key, bool forgot, uint32_t L) {
   const uint64_t thr = frontier_at<KPL>(F, L - 1);
   const bool pass = key < thr;
@@ -156,18 +167,13 @@ __device__ __forceinline__ void merge_keys(uint64_t (&F)[KPL], uint64_t key, boo
       pm &= pm - 1;
       insert_key<KPL>(F, readlane64(key, lane));
     }
-  } else if constexpr (KPL == 1) {
-    F[0] = sort_merge_1(F[0], key, forgot);
   } else {
-    uint64_t cc[1] = {key};
-    bitonic_sort<1, true>(cc);
-    if (!forgot) {
-      // no node can repeat: the P smallest of F and C are min(F, C reversed)
-      F[KPL - 1] = min64(F[KPL - 1], cc[0]);
-      bitonic_merge_up<KPL>(F);
-    } else {
-      merge_dedupe<KPL>(F, cc[0]);
-    }
+    FrontierRegs<KPL> x;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) x.f[r] = F[r];
+    x = CALL ? sort_merge_call<KPL>(x, key, forgot) : sort_merge<KPL>(x, key, forgot);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) F[r] = x.f[r];
   }
   const uint32_t l = lane_id();
 #pragma unroll

@@ -183,7 +183,7 @@ extern "C" gorio_status gorio_build_index(gorio_dtype dtype, const void *vectors
 
   // pack into HBM
   const uint64_t index_bytes = ix->num_pages * (uint64_t)page_bytes;
-  HIP_OR_FAIL(hipMalloc(&ix->d_pages, index_bytes));
+  HIP_OR_FAIL(hipMalloc(&ix->d_pages, index_bytes + kPageSlack));
   fill_u32<<<grid_for(index_bytes / 4, 256), 256, 0, s>>>(reinterpret_cast<uint32_t *>(ix->d_pages),
                                                           index_bytes / 4, 0u);
   PageGeom geom = ix->geom();

@@ -235,7 +235,7 @@ struct gorio_index {
   // All pages to HBM (from the backing store if paged).
   gorio_status make_resident() {
     if (resident) return GORIO_OK;
-    hipError_t e = hipMalloc(&d_pages, index_bytes());
+    hipError_t e = hipMalloc(&d_pages, index_bytes() + gorio::kPageSlack);
     if (e != hipSuccess) return gorio::fail(GORIO_ENOMEM, "hipMalloc of %llu page bytes failed",
                                             (unsigned long long)index_bytes());
     e = hipMemcpy(d_pages, h_backing, index_bytes(), hipMemcpyHostToDevice);

@@ -33,7 +33,7 @@ inline uint32_t lane_state_words(uint32_t L) {
   return (uint32_t)((b + 3) / 4);
 }
 
-// Visited tables of the resident kernel: 16-bit entries (2^M::kHtLog2 of
+// Visited tables of the resident kernel: 16-bit entries (2^M::ht_log2 of
 // them) when every id fits that table's domain, else 8192 32-bit entries.
 using ResidentHtLarge = VisitedLds<13>;
 
@@ -61,10 +61,13 @@ hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s
 
 template <int KPL, class M, bool N2S>
 hipError_t resident_t(const ResidentParams &p, int grid, hipStream_t s) {
-  using Small = VisitedLds16<M::kHtLog2>;
-  constexpr int kGrid = M::kGridWavesPerSimd;
-  if (p.n <= Small::kMaxId) return launch_resident_grid<search_resident<KPL, M, Small, N2S>, kGrid>(p, grid, s);
-  return launch_resident_grid<search_resident<KPL, M, ResidentHtLarge, N2S>, kGrid>(p, grid, s);
+  using Small = VisitedLds16<M::ht_log2(KPL)>;
+  constexpr int kGrid = M::grid_waves_per_simd(KPL);
+  if (M::kSmallIds || p.n <= Small::kMaxId)
+    return launch_resident_grid<search_resident<KPL, M, Small, N2S>, kGrid>(p, grid, s);
+  if constexpr (!M::kSmallIds)
+    return launch_resident_grid<search_resident<KPL, M, ResidentHtLarge, N2S>, kGrid>(p, grid, s);
+  return hipErrorInvalidValue;  // not reached: the caller checks p.n
 }
 
 // frontier slots per lane (L <= 64 KPL) and node_to_slot presence

@@ -8,9 +8,11 @@
 //
 //   MetricU8  - exact int32 distance: q.q + sum (x.x - 2 q.x) with
 //               v_dot4_u32_u8 on coalesced reads, 8 lanes per vector.
-//   MetricF32 - one lane per candidate (resident 96-d rows are gathered 8
-//               lanes per vector by whole lines and handed to their lanes
-//               through LDS);
+//   MetricU8Rows - the same for rows of other lengths, arrangements and
+//               placements (resident).
+//   MetricF32, MetricF32Lines - one lane per candidate (the resident kernel
+//               gathers 8 lanes per vector by whole lines and hands the
+//               blocks to their lanes through LDS);
 //               t = q_d - x_d, acc = acc + t*t for d = 0 .. D-1 in order,
 //               every operation rounded to nearest even with no fused
 //               multiply-add, so the result is the same float as a plain
@@ -39,19 +41,31 @@ struct MetricU8 {
   static constexpr int kChunks = kBatch / kWave;
   static_assert(kRounds % 8 == 0, "rounds are reduced eight at a time");
   static constexpr int kQueryWords = 1;          // the query lives in registers
-  // resident kernel: waves per SIMD and the 16-bit visited table that fits
-  // them (4 waves: <= 128 registers, 4096 entries in 8 KB of LDS)
-  static constexpr int kWavesPerSimd = VDW <= 4 ? 4 : 2;
-  static constexpr int kHtLog2 = VDW <= 4 ? 12 : 13;
-  // Waves per SIMD in the resident grid.  Two keep the gathers saturated
-  // (a 100k-query batch on the 1M x 128-d index runs at the same rate with
-  // two or four per SIMD); with two, each query finishes sooner and so does
-  // a batch's tail, when the query counter has run dry and the chip empties
-  // (10k queries: 0.79 ms against 0.85 ms with four).
-  static constexpr int kGridWavesPerSimd = 2;
+  // resident kernel: waves per SIMD (registers, LDS), those of the grid, and
+  // the 16-bit visited table.  Frontiers of up to 64: 4096 entries in 8 KB and
+  // 128 registers; the grid holds two waves per SIMD, which keep the gathers
+  // saturated (a 100k-query batch on the 1M x 128-d index runs at the same
+  // rate with two or four per SIMD) while each query, and so a batch's tail,
+  // finishes sooner (10k queries: 0.79 ms against 0.85 ms with four).  Longer
+  // frontiers meet more nodes than 4096 entries record (L=128, W=8, R=64: 80M
+  // of 148M evaluations were repeats), and two waves per SIMD leave room for
+  // 16 KB each.
+  __host__ __device__ static constexpr int waves_per_simd(int kpl) { return VDW <= 4 && kpl == 1 ? 4 : 2; }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int) { return 2; }
+  __host__ __device__ static constexpr int ht_log2(int kpl) { return VDW <= 4 && kpl == 1 ? 12 : 13; }
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;  // INT32_MAX
   static_assert(!LOC16 || (EXACT && VDW % 4 == 0), "locators address whole 16-byte units");
   static constexpr bool kLocators = LOC16;
+  static constexpr bool kSmallIds = false;
+  static constexpr bool kStream = LOC16;    // chunks of 64, two in flight
+  static constexpr bool kOffsets = false;   // candidates' byte offsets kept in LDS
+  __host__ __device__ static constexpr int stage_words(int) { return 0; }  // LDS of a wave for set_stage
+  // search_team (locators): waves per query, per SIMD at least, visited table
+  __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 ? 8 : 4; }
+  __host__ __device__ static constexpr int team_per_simd() { return 2; }
+  __host__ __device__ static constexpr int team_ht_log2(int) { return 13; }
+  static constexpr int kTeamStageWords = 0;
+  __device__ __forceinline__ void set_stage(uint32_t *) {}
   static constexpr bool kGathered = false;  // float32 line gather only
 
   // Where the kernel's compaction puts the i-th new candidate, and the word
@@ -70,7 +84,8 @@ struct MetricU8 {
   // After compaction of cnt candidates: give the rest of the last chunk of 64
   // the fallback node's word, so that every lane of every round of a chunk
   // loads a vector (the chunk's load count is then fixed).
-  __device__ __forceinline__ static void pad_round(uint32_t *cand, uint32_t cnt, uint32_t fallback_word) {
+  __device__ __forceinline__ static void pad_round(uint32_t *cand, uint64_t *, uint32_t cnt, uint32_t fallback_word,
+                                                   uint64_t) {
     if constexpr (LOC16) {
       const uint32_t i = cnt + (uint32_t)lane_id();
       if (i < ((cnt + kWave - 1) & ~(uint32_t)(kWave - 1))) cand[cand_pos(i)] = fallback_word;
@@ -92,7 +107,8 @@ struct MetricU8 {
   }
 
   // Distance bits of one record, computed by the whole wave (uniform result).
-  __device__ __forceinline__ uint32_t dist_one(const uint8_t *rec) const {
+  __device__ __forceinline__ uint32_t dist_one(const uint8_t *pages, uint64_t off) const {
+    const uint8_t *rec = pages + off;
     U8Vec<VDW, EXACT> x;
     x.load(rec, lane_id() & 7, dwords);
     return (uint32_t)(sum8(partial_u8(q, x)) + qq);
@@ -150,8 +166,9 @@ struct MetricU8 {
   struct Chunk {
     U8Vec<VDW, EXACT> x[8];
   };
-  __device__ __forceinline__ void chunk_issue(__amdgpu_buffer_rsrc_t rs, const uint32_t *cand, uint32_t c0,
-                                              Chunk &ck) const {
+  __device__ __forceinline__ void chunk_issue(const uint8_t *pages, const PageGeom &geom, const uint32_t *cand,
+                                              const uint64_t *, uint32_t c0, Chunk &ck) const {
+    const __amdgpu_buffer_rsrc_t rs = units16_rsrc(pages, geom);
     static_assert(LOC16 && kRounds == 16, "streaming needs locators and 16 rounds per 128 candidates");
     const int l = lane_id();
     const int g = l >> 3;
@@ -247,33 +264,131 @@ struct MetricU8 {
 };
 
 // ---------------------------------------------------------------------------
+// uint8 rows of any length from 16 bytes up, any arrangement and placement
+// (resident kernel; identity-placed 128-byte rows on line starts are MetricU8
+// with locators).  8 lanes per vector; lane gl holds the 16-byte units
+// gl + 8 t, so each load instruction reads whole lines.  The last unit of a
+// ragged row starts 16 bytes before the row's end and masks the bytes that the
+// unit before it has already, so nothing past the row is read and every
+// dimension counts once.  Candidates' byte offsets are worked out once, when
+// they are compacted, and read back from LDS; two chunks of 64 vectors are in
+// flight.  (Dword loads with a bound check on each, and the placement looked
+// up between compaction and gather: 300k x 100, contiguous, placed, 5,000
+// queries 620 us a launch.)
+// ---------------------------------------------------------------------------
+template <int NU, bool EXACT>
+struct MetricU8Rows {
+  static constexpr int kQueryWords = 1;
+  // two waves per SIMD: 256 registers, 16 KB visited table
+  __host__ __device__ static constexpr int waves_per_simd(int) { return 2; }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int) { return 2; }
+  __host__ __device__ static constexpr int ht_log2(int) { return 13; }
+  static constexpr uint32_t kPadDist = 0x7FFFFFFFu;
+  static constexpr bool kLocators = false, kGathered = false, kStream = true, kOffsets = true;
+  static constexpr bool kSmallIds = false;
+  __host__ __device__ static constexpr int stage_words(int) { return 0; }
+  __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 ? 8 : 4; }
+  __host__ __device__ static constexpr int team_per_simd() { return 2; }
+  __host__ __device__ static constexpr int team_ht_log2(int) { return 13; }
+  static constexpr int kTeamStageWords = 0;
+  __device__ __forceinline__ void set_stage(uint32_t *) {}
+
+  __device__ __forceinline__ static uint32_t cand_pos(uint32_t i) { return i; }
+  __device__ __forceinline__ static uint32_t cand_word(const PageGeom &, uint32_t v) { return v; }
+  // the rest of the last chunk reads the fallback vector
+  __device__ __forceinline__ static void pad_round(uint32_t *, uint64_t *coff, uint32_t cnt, uint32_t,
+                                                   uint64_t fallback_off) {
+    const uint32_t i = cnt + (uint32_t)lane_id();
+    if (i < ((cnt + kWave - 1) & ~(uint32_t)(kWave - 1))) coff[i] = fallback_off;
+  }
+
+  uint32_t q[NU * 4], mask[EXACT ? 1 : NU * 4];
+  uint32_t start[NU];  // byte offset of unit t in a row
+  int qq;
+
+  struct Row {
+    uint32_t w[NU * 4];
+  };
+  __device__ __forceinline__ void load_row(const uint8_t *row, Row &x) const {
+#pragma unroll
+    for (int t = 0; t < NU; ++t) {
+      uint4 u;
+      __builtin_memcpy(&u, __builtin_assume_aligned(row + start[t], 4), 16);
+      x.w[4 * t] = u.x; x.w[4 * t + 1] = u.y; x.w[4 * t + 2] = u.z; x.w[4 * t + 3] = u.w;
+    }
+  }
+  __device__ __forceinline__ void load_query(const void *queries, uint32_t qi, uint32_t D, uint32_t *) {
+    const uint32_t gl = lane_id() & 7;
+#pragma unroll
+    for (int t = 0; t < NU; ++t) {
+      const uint32_t at = 16u * (gl + 8u * t);
+      start[t] = EXACT ? at : min(at, D - 16u);
+      if constexpr (!EXACT) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mask[4 * t + j] = at < D && start[t] + 4u * j >= at ? 0xFFFFFFFFu : 0u;
+      }
+    }
+    Row x;
+    load_row(static_cast<const uint8_t *>(queries) + (uint64_t)qi * D, x);
+    int s = 0;
+#pragma unroll
+    for (int t = 0; t < NU * 4; ++t) {
+      q[t] = EXACT ? x.w[t] : x.w[t] & mask[t];
+      s += (int)__builtin_amdgcn_udot4(q[t], q[t], 0u, false);
+    }
+    qq = sum8(s);
+  }
+  __device__ __forceinline__ int partial(const Row &x) const {
+    uint32_t xx = 0, qx = 0;
+#pragma unroll
+    for (int t = 0; t < NU * 4; ++t) {
+      const uint32_t w = EXACT ? x.w[t] : x.w[t] & mask[t];
+      xx = __builtin_amdgcn_udot4(w, w, xx, false);
+      qx = __builtin_amdgcn_udot4(q[t], w, qx, false);
+    }
+    return (int)xx - 2 * (int)qx;
+  }
+  __device__ __forceinline__ uint32_t dist_one(const uint8_t *pages, uint64_t off) const {
+    Row x;
+    load_row(pages + off, x);
+    return (uint32_t)(sum8(partial(x)) + qq);
+  }
+
+  // Group g reads candidates c0 + 8 g .. + 7, so lane l ends with candidate
+  // c0 + l.
+  struct Chunk {
+    Row x[8];
+  };
+  __device__ __forceinline__ void chunk_issue(const uint8_t *pages, const PageGeom &, const uint32_t *,
+                                              const uint64_t *coff, uint32_t c0, Chunk &ck) const {
+    const uint64_t *o = coff + c0 + (lane_id() & ~7);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) load_row(pages + o[r], ck.x[r]);
+  }
+  __device__ __forceinline__ uint64_t chunk_key(const PageGeom &, const uint32_t *cand, uint32_t c0, uint32_t cnt,
+                                                const Chunk &ck) const {
+    int part[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) part[r] = partial(ck.x[r]);
+    const int dist = transpose_sum8(part) + qq;
+    const uint32_t i = c0 + lane_id();
+    return i < cnt ? (((uint64_t)(uint32_t)dist << 32) | ((uint64_t)cand[i] << 1)) : kInfKey;
+  }
+};
+
+// ---------------------------------------------------------------------------
 // float32
 // ---------------------------------------------------------------------------
 // NV4: the vector has at most 4 * NV4 floats.  EXACT: exactly 4 * NV4, read
 // with 16-B loads all at once; otherwise dword loads of d < D, 16 at a time.
 template <int NV4, bool EXACT>
-struct MetricF32 {
-  static constexpr int kBatch = kWave;  // one candidate per lane
-  static constexpr int kChunks = 1;
+struct MetricF32 {  // paged kernels: one lane per candidate, records in the page cache
   static constexpr int kQueryWords = 4 * NV4;
   static constexpr uint32_t kPadDist = 0x7F800000u;  // +inf
-  // resident kernel: 96-d rows (gathered by lines, blocks staged through a
-  // 4 KB LDS buffer) keep two batches of lines in registers, which fits one
-  // wave per SIMD and leaves LDS for a 32 KB visited table; other widths run
-  // two waves per SIMD with a 16 KB table
-  static constexpr bool kGathered = EXACT && NV4 % 8 == 0;
-  static constexpr int kWavesPerSimd = kGathered ? 1 : 2;
-  static constexpr int kHtLog2 = kGathered ? 14 : 13;
-  static constexpr int kGridWavesPerSimd = kWavesPerSimd;
   static constexpr int kStep = 16;                   // dwords per round trip (generic path)
 
   const float *qs;  // the query in LDS (wave-uniform reads)
   uint32_t D;
-
-  static constexpr bool kLocators = false;
-  __device__ __forceinline__ static void pad_round(uint32_t *, uint32_t, uint32_t) {}
-  __device__ __forceinline__ static uint32_t cand_pos(uint32_t i) { return i; }
-  __device__ __forceinline__ static uint32_t cand_word(const PageGeom &, uint32_t v) { return v; }
 
   // Copies the query into LDS; the caller synchronizes before use.
   __device__ __forceinline__ void load_query(const void *queries, uint32_t qi, uint32_t D_, uint32_t *qlds) {
@@ -319,148 +434,9 @@ struct MetricF32 {
     return acc;
   }
 
-  __device__ __forceinline__ float dist_global(const uint8_t *rec) const {
-    const uint32_t *w = reinterpret_cast<const uint32_t *>(rec);
-    return dist_lane(
-        [&](int i) {
-          uint4 u;
-          __builtin_memcpy(&u, __builtin_assume_aligned(w + 4 * i, 4), 16);
-          return u;
-        },
-        [&](uint32_t d) { return w[d]; });
-  }
-
   __device__ __forceinline__ float dist_cached(__amdgpu_buffer_rsrc_t r, uint32_t off) const {
     return dist_lane([&](int i) { return coherent_load_u128(r, off + 16u * (uint32_t)i); },
                      [&](uint32_t d) { return coherent_load_u32(r, off + 4u * d); });
-  }
-
-  // Distance bits of one record (lane 0 computes, the result is broadcast).
-  __device__ __forceinline__ uint32_t dist_one(const uint8_t *rec) const {
-    uint32_t b = 0;
-    if (lane_id() == 0) b = __float_as_uint(dist_global(rec));
-    return first_lane_value(b);
-  }
-
-  template <bool N2S>
-  __device__ __forceinline__ void resident_keys(const uint8_t *pages, const PageGeom &geom, const uint32_t *cand,
-                                                uint32_t c0, uint32_t cnt, uint32_t fallback,
-                                                uint64_t (&key)[kChunks]) const {
-    const uint32_t idx = c0 + lane_id();
-    const uint32_t node = idx < cnt ? cand[idx] : fallback;
-    const uint64_t off = vec_offset(geom, slot_ct<N2S>(geom, node));
-    if constexpr (kGathered) {
-      const uint32_t c = transposed_candidate();
-      const float d = dist_gathered(pages, off);
-      const uint32_t cn = (uint32_t)__shfl((int)node, (int)c);
-      key[0] = c0 + c < cnt ? (((uint64_t)__float_as_uint(d) << 32) | ((uint64_t)cn << 1)) : kInfKey;
-    } else {
-      const float d = dist_global(pages + off);
-      key[0] = idx < cnt ? (((uint64_t)__float_as_uint(d) << 32) | ((uint64_t)node << 1)) : kInfKey;
-    }
-  }
-
-  // Resident gather of 64 vectors, lane i's vector at byte offset `off` of
-  // lane i.  One lane reading a whole vector would make every 16-byte load
-  // instruction touch 64 different cache lines; instead the 8 lanes of a
-  // group read 8 vectors, one at a time, each lane 16 bytes of every 128
-  // (so each load instruction covers whole lines).  The 16-byte blocks then
-  // pass through LDS, half a batch at a time (32 vectors x 128 bytes = 4 KB),
-  // so that each lane gets one 128-byte line of its own candidate's vector
-  // for the sequential sum: no VALU work moves the blocks, and the LDS
-  // traffic runs beside the arithmetic.  Lane i ends with candidate i.
-  __device__ __forceinline__ static uint32_t transposed_candidate() { return lane_id(); }
-
-  // Block k of LDS row t sits at 16-byte position k ^ ((t >> 1) & 7): the
-  // writes of one round cover 1 KB contiguously and the reads (lane t, row
-  // t) spread any 16 consecutive lanes over all 64 banks.
-  __device__ __forceinline__ static uint32_t tpos(uint32_t row, uint32_t k) { return row * 8u + (k ^ ((row >> 1) & 7u)); }
-
-  // Line j of the vectors of the group's 8 candidates: x[r][c] = float
-  // 32 j + 4 gl + c of the vector of lane r * 8 + g.
-  __device__ __forceinline__ static void load_line(const uint8_t *pages, uint64_t off, int j, uint32_t (&x)[8][4]) {
-    const uint32_t l = lane_id(), g = l >> 3, gl = l & 7u;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const uint64_t o = __shfl(off, r * 8 + (int)g);
-      const uint32_t *w = reinterpret_cast<const uint32_t *>(pages + o) + 32 * j + 4 * gl;
-      uint4 u;
-      __builtin_memcpy(&u, __builtin_assume_aligned(w, 4), 16);
-      x[r][0] = u.x;
-      x[r][1] = u.y;
-      x[r][2] = u.z;
-      x[r][3] = u.w;
-    }
-  }
-
-  // acc over line j of this lane's vector.  x[r] holds block gl of line j of
-  // the vector of lane r * 8 + g; through LDS, lane i receives y[k] = block k
-  // of its own vector's line (floats 32 j + 4 k .. + 3), so k then the
-  // component visits d in increasing order.
-  __device__ __forceinline__ float sum_line(float acc, uint32_t (&x)[8][4], int j) const {
-    __shared__ __align__(16) uint4 stage[32 * 8];
-    const uint32_t l = lane_id(), g = l >> 3, gl = l & 7u, t = l & 31u;
-    uint4 y[8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const uint32_t row = (uint32_t)rr * 8u + g;
-        stage[tpos(row, gl)] = make_uint4(x[4 * h + rr][0], x[4 * h + rr][1], x[4 * h + rr][2], x[4 * h + rr][3]);
-      }
-      if ((l >> 5) == (uint32_t)h) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) y[k] = stage[tpos(t, (uint32_t)k)];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float4 qv = *reinterpret_cast<const float4 *>(qs + 32 * j + 4 * k);
-      acc = step(acc, qv.x, __uint_as_float(y[k].x));
-      acc = step(acc, qv.y, __uint_as_float(y[k].y));
-      acc = step(acc, qv.z, __uint_as_float(y[k].z));
-      acc = step(acc, qv.w, __uint_as_float(y[k].w));
-    }
-    return acc;
-  }
-
-  // One batch of 64 candidates' vectors in flight (resident kernel, line
-  // gather): the loads are issued by gather_issue and consumed by gather_key,
-  // so that another batch's loads can be outstanding in between.
-  struct Gathered {
-    uint32_t x[NV4 / 8][8][4];
-    uint32_t node;
-  };
-
-  template <bool N2S>
-  __device__ __forceinline__ static void gather_issue(const uint8_t *pages, const PageGeom &geom, const uint32_t *cand,
-                                                      uint32_t c0, uint32_t cnt, uint32_t fallback, Gathered &b) {
-    const uint32_t idx = c0 + lane_id();
-    b.node = idx < cnt ? cand[idx] : fallback;
-    const uint64_t off = vec_offset(geom, slot_ct<N2S>(geom, b.node));
-#pragma unroll
-    for (int j = 0; j < NV4 / 8; ++j) load_line(pages, off, j, b.x[j]);
-  }
-
-  __device__ __forceinline__ uint64_t gather_key(Gathered &b, uint32_t c0, uint32_t cnt) const {
-    float acc = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NV4 / 8; ++j) acc = sum_line(acc, b.x[j], j);
-    const uint32_t c = transposed_candidate();
-    const uint32_t cn = (uint32_t)__shfl((int)b.node, (int)c);
-    return c0 + c < cnt ? (((uint64_t)__float_as_uint(acc) << 32) | ((uint64_t)cn << 1)) : kInfKey;
-  }
-
-  __device__ __forceinline__ float dist_gathered(const uint8_t *pages, uint64_t off) const {
-    static_assert(EXACT && NV4 % 8 == 0, "whole 128-byte lines per vector");
-    constexpr int J = NV4 / 8;  // lines per vector, all in flight at once
-    uint32_t x[J][8][4];
-#pragma unroll
-    for (int j = 0; j < J; ++j) load_line(pages, off, j, x[j]);
-    float acc = 0.0f;
-#pragma unroll
-    for (int j = 0; j < J; ++j) acc = sum_line(acc, x[j], j);
-    return acc;
   }
 
   template <class OffOf>
@@ -473,6 +449,194 @@ struct MetricF32 {
       key = ((uint64_t)__float_as_uint(d) << 32) | ((uint64_t)node << 1);
     }
     return key;
+  }
+};
+
+// Resident kernel: rows of at most 32 J floats (J lines of 128 bytes), any
+// arrangement and placement.  One lane sums a candidate's whole vector, but a
+// lane that reads its own vector makes every 16-byte load instruction touch 64
+// different lines; so the 8 lanes of a group read 8 vectors, one at a time,
+// each lane 16 bytes of every 128, and the 16-byte blocks pass through LDS, 16
+// vectors at a time, so that each lane gets the line of its own vector for the
+// sequential sum (no VALU work moves them).  The lines of one batch of 64
+// vectors are in flight at any time: as a line is taken out of its registers
+// the same line of the next batch is read into them.
+// EXACT: every line is whole (D = 32 J); for the 16-bit visited tables only.
+template <int J, bool EXACT = false>
+struct MetricF32Lines {
+  static constexpr int kQueryWords = 32 * J;
+  static constexpr uint32_t kPadDist = 0x7F800000u;  // +inf
+  // A line takes 32 registers: up to four lines, two waves per SIMD.  Long
+  // frontiers meet more nodes than a 16 KB visited table records, and 32 KB
+  // leave room for one.
+  __host__ __device__ static constexpr int waves_per_simd(int kpl) { return J <= 4 && kpl == 1 ? 2 : 1; }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int kpl) { return waves_per_simd(kpl); }
+  __host__ __device__ static constexpr int ht_log2(int kpl) { return waves_per_simd(kpl) == 2 ? 13 : 14; }
+  // With one wave per SIMD nothing else covers the LDS passes and the sums, so
+  // such a kernel is given room (`roomy`): 32 vectors per LDS pass, and the
+  // compiler may overlap one line's sums with the next lines' passes and keep
+  // the query in registers; for whole lines two batches are in flight (1M x
+  // 96, L=128, W=8, 10k queries: 5.27 ms without any of it, 4.83 with the
+  // ragged line's tests, 4.18 now).
+  __host__ __device__ static constexpr bool roomy(int kpl) { return waves_per_simd(kpl) == 1 && J <= 4; }
+  __host__ __device__ static constexpr bool two_batches(int kpl) { return EXACT && kpl == 2; }
+  __host__ __device__ static constexpr int stage_words(int kpl) { return roomy(kpl) ? 1024 : 512; }
+  static constexpr bool kLocators = false, kStream = false, kOffsets = false, kGathered = true;
+  static constexpr bool kSmallIds = EXACT;  // only indexes whose ids fit the 16-bit tables
+
+  __device__ __forceinline__ static void pad_round(uint32_t *, uint64_t *, uint32_t, uint32_t, uint64_t) {}
+  __device__ __forceinline__ static uint32_t cand_pos(uint32_t i) { return i; }
+  __device__ __forceinline__ static uint32_t cand_word(const PageGeom &, uint32_t v) { return v; }
+
+  // search_team: waves per query, and per SIMD at least
+  __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 && J <= 4 ? 8 : 4; }
+  __host__ __device__ static constexpr int team_per_simd() { return J <= 4 ? 2 : 1; }
+  __host__ __device__ static constexpr int team_ht_log2(int kpl) { return kpl > 1 ? 14 : 13; }
+  static constexpr int kTeamStageWords = 512;
+
+  const float *qs;  // the query in LDS (wave-uniform reads), zeros past D
+  uint4 *stage;     // LDS for sum_line, this wave's own: 1 KB per 8 vectors of a pass
+  uint32_t D;
+
+  __device__ __forceinline__ void set_stage(uint32_t *st) { stage = reinterpret_cast<uint4 *>(st); }
+
+  // Copies the query into LDS; the caller synchronizes before use.
+  __device__ __forceinline__ void load_query(const void *queries, uint32_t qi, uint32_t D_, uint32_t *qlds) {
+    D = D_;
+    const uint32_t *src = static_cast<const uint32_t *>(queries) + (uint64_t)qi * D_;
+#pragma unroll
+    for (uint32_t d0 = 0; d0 < (uint32_t)kQueryWords; d0 += kWave) {
+      const uint32_t d = d0 + lane_id();
+      if (d < (uint32_t)kQueryWords) qlds[d] = d < D_ ? src[d] : 0u;
+    }
+    qs = reinterpret_cast<const float *>(qlds);
+  }
+
+  // acc + (q_d - x_d)^2 for one element, each step rounded on its own
+  __device__ __forceinline__ static float step(float acc, float qd, uint32_t xd) {
+    const float t = __fsub_rn(qd, __uint_as_float(xd));
+    return __fadd_rn(acc, __fmul_rn(t, t));
+  }
+
+  struct Line {
+    uint32_t x[8][4];
+  };
+  struct Batch {
+    Line line[J];
+  };
+
+  // Line j of the vectors of the group's 8 candidates: x[r][c] = float
+  // 32 j + 4 gl + c of the vector of lane r * 8 + g (byte offset `off` in lane
+  // r * 8 + g).  Blocks past the vector's last read the last one again; that
+  // one may reach up to 12 bytes past the vector (the page array ends with
+  // 16 spare bytes).
+  __device__ __forceinline__ void load_line(const uint8_t *pages, uint64_t off, int j, Line &ln) const {
+    const uint32_t l = lane_id(), g = l >> 3, gl = l & 7u;
+    const uint32_t at = EXACT || j + 1 < J ? 32u * j + 4u * gl : min(32u * j + 4u * gl, (D - 1u) & ~3u);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const uint64_t o = __shfl(off, r * 8 + (int)g);
+      const uint32_t *w = reinterpret_cast<const uint32_t *>(pages + o) + at;
+      uint4 u;
+      __builtin_memcpy(&u, __builtin_assume_aligned(w, 4), 16);
+      ln.x[r][0] = u.x;
+      ln.x[r][1] = u.y;
+      ln.x[r][2] = u.z;
+      ln.x[r][3] = u.w;
+    }
+  }
+
+  // Block k of LDS row t sits at 16-byte position k ^ ((t >> 1) & 7): the
+  // writes of one round cover 1 KB contiguously and the reads (lane t, row
+  // t) spread 16 consecutive lanes over all 64 banks.
+  __device__ __forceinline__ static uint32_t tpos(uint32_t row, uint32_t k) { return row * 8u + (k ^ ((row >> 1) & 7u)); }
+
+  // acc over line j of this lane's vector: through LDS, lane i receives
+  // y[k] = block k of its own vector's line (floats 32 j + 4 k .. + 3), so k
+  // then the component visits d in increasing order.
+  template <bool ROOMY>
+  __device__ __forceinline__ float sum_line(float acc, const Line &ln, int j) const {
+    constexpr uint32_t kRows = ROOMY ? 32 : 16;  // vectors per pass
+    const uint32_t l = lane_id(), g = l >> 3, gl = l & 7u, t = l & (kRows - 1);
+    uint4 y[8];
+#pragma unroll
+    for (uint32_t h = 0; h < kWave / kRows; ++h) {
+#pragma unroll
+      for (uint32_t rr = 0; rr < kRows / 8; ++rr) {
+        const uint32_t r = h * (kRows / 8) + rr;
+        stage[tpos(rr * 8u + g, gl)] = make_uint4(ln.x[r][0], ln.x[r][1], ln.x[r][2], ln.x[r][3]);
+      }
+      if (l / kRows == h) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) y[k] = stage[tpos(t, (uint32_t)k)];
+      }
+    }
+    // the line's part of the query, read where it is used: taken out of the
+    // loop over batches, the whole query would hold 32 registers per line
+    int q0 = 32 * j;
+    if constexpr (!ROOMY) asm volatile("" : "+s"(q0));
+    if (EXACT || j + 1 < J) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc = step4(acc, q0 + 4 * k, y[k]);
+    } else {
+      // the vector's last line: rem floats; the query is 0 past them and so
+      // is x made, which leaves the sum as it is
+      const uint32_t rem = D - 32u * j;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (4u * k >= rem) break;
+        if (4u * k + 4u > rem) {
+          if (4u * k + 1u >= rem) y[k].y = 0u;
+          if (4u * k + 2u >= rem) y[k].z = 0u;
+          y[k].w = 0u;
+        }
+        acc = step4(acc, q0 + 4 * k, y[k]);
+      }
+    }
+    // the line is summed here: sunk to where the distance is used, the sums
+    // would keep every line's y until then
+    if constexpr (!ROOMY) asm volatile("" : "+v"(acc));
+    return acc;
+  }
+  __device__ __forceinline__ float step4(float acc, int d, const uint4 &x) const {
+    const float4 qv = *reinterpret_cast<const float4 *>(qs + d);
+    acc = step(acc, qv.x, x.x);
+    acc = step(acc, qv.y, x.y);
+    acc = step(acc, qv.z, x.z);
+    return step(acc, qv.w, x.w);
+  }
+
+  __device__ __forceinline__ void issue(const uint8_t *pages, uint64_t off, Batch &b) const {
+#pragma unroll
+    for (int j = 0; j < J; ++j) load_line(pages, off, j, b.line[j]);
+  }
+  // Distance bits of the batch in b; the vectors at `next` take its place.
+  template <bool ROOMY>
+  __device__ __forceinline__ uint32_t dist_and_issue(const uint8_t *pages, uint64_t next, Batch &b) const {
+    float acc = 0.0f;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      acc = sum_line<ROOMY>(acc, b.line[j], j);
+      if constexpr (!ROOMY) {
+        load_line(pages, next, j, b.line[j]);
+        __builtin_amdgcn_sched_barrier(0);  // no load moves ahead of the line it replaces
+      }
+    }
+    if constexpr (ROOMY) issue(pages, next, b);
+    return __float_as_uint(acc);
+  }
+  template <bool ROOMY>
+  __device__ __forceinline__ uint32_t dist(const Batch &b) const {
+    float acc = 0.0f;
+#pragma unroll
+    for (int j = 0; j < J; ++j) acc = sum_line<ROOMY>(acc, b.line[j], j);
+    return __float_as_uint(acc);
+  }
+  // Distance bits of one record (`off` the same in every lane).
+  __device__ __forceinline__ uint32_t dist_one(const uint8_t *pages, uint64_t off) const {
+    Batch b;
+    issue(pages, off, b);
+    return dist<false>(b);
   }
 };
 

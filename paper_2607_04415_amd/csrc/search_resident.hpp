@@ -49,70 +49,94 @@ struct ResidentParams {
   unsigned long long next_base;
 };
 
-// Evaluates NCH chunks of 64 compacted candidates (locator metrics) and
+// Evaluates NCH chunks of 64 compacted candidates (streaming metrics) and
 // merges their keys into F, with two chunks in flight.
 template <int NCH, int KPL, class M>
-__device__ __forceinline__ void eval_chunks(const M &m, const ResidentParams &p, const uint32_t *cand, uint32_t cnt,
-                                            uint64_t (&F)[KPL], bool forgot) {
-  const __amdgpu_buffer_rsrc_t rs = units16_rsrc(p.pages, p.geom);
+__device__ __forceinline__ void eval_chunks(const M &m, const ResidentParams &p, const uint32_t *cand,
+                                            const uint64_t *coff, uint32_t cnt, uint64_t (&F)[KPL], bool forgot) {
   typename M::Chunk A, B;
-  m.chunk_issue(rs, cand, 0, A);
-  if constexpr (NCH > 1) m.chunk_issue(rs, cand, kWave, B);
+  m.chunk_issue(p.pages, p.geom, cand, coff, 0, A);
+  if constexpr (NCH > 1) m.chunk_issue(p.pages, p.geom, cand, coff, kWave, B);
   uint64_t key = m.chunk_key(p.geom, cand, 0, cnt, A);
-  if constexpr (NCH > 2) m.chunk_issue(rs, cand, 2 * kWave, A);
+  if constexpr (NCH > 2) m.chunk_issue(p.pages, p.geom, cand, coff, 2 * kWave, A);
   merge_keys<KPL>(F, key, forgot, p.L);
   if constexpr (NCH > 1) {
     key = m.chunk_key(p.geom, cand, kWave, cnt, B);
-    if constexpr (NCH > 3) m.chunk_issue(rs, cand, 3 * kWave, B);
+    if constexpr (NCH > 3) m.chunk_issue(p.pages, p.geom, cand, coff, 3 * kWave, B);
     merge_keys<KPL>(F, key, forgot, p.L);
   }
   if constexpr (NCH > 2) merge_keys<KPL>(F, m.chunk_key(p.geom, cand, 2 * kWave, cnt, A), forgot, p.L);
   if constexpr (NCH > 3) merge_keys<KPL>(F, m.chunk_key(p.geom, cand, 3 * kWave, cnt, B), forgot, p.L);
 }
 
-// Evaluates NCH batches of 64 compacted candidates with the float32 line
-// gather and merges their keys into F, two batches in flight (the same
-// fixed schedule as eval_chunks).
-template <int NCH, int KPL, bool N2S, class M>
-__device__ __forceinline__ void eval_gathered(const M &m, const ResidentParams &p, const uint32_t *cand, uint32_t cnt,
-                                              uint64_t (&F)[KPL], bool forgot) {
-  typename M::Gathered A, B;
-  M::template gather_issue<N2S>(p.pages, p.geom, cand, 0, cnt, p.entry, A);
-  if constexpr (NCH > 1) M::template gather_issue<N2S>(p.pages, p.geom, cand, kWave, cnt, p.entry, B);
-  uint64_t key = m.gather_key(A, 0, cnt);
-  if constexpr (NCH > 2) M::template gather_issue<N2S>(p.pages, p.geom, cand, 2 * kWave, cnt, p.entry, A);
-  merge_keys<KPL>(F, key, forgot, p.L);
-  if constexpr (NCH > 1) {
-    key = m.gather_key(B, kWave, cnt);
-    if constexpr (NCH > 3) M::template gather_issue<N2S>(p.pages, p.geom, cand, 3 * kWave, cnt, p.entry, B);
-    merge_keys<KPL>(F, key, forgot, p.L);
+// Evaluates cnt > 0 compacted candidates with the float32 line gather, 64 at a
+// time, and merges their keys into F; off_of(i) is candidate i's byte offset.
+// The last batch has its own copy so that every batch before it issues the
+// same loads and the waits stay exact.
+template <int KPL, class M, class OffOf>
+__device__ __forceinline__ void eval_lines(const M &m, const ResidentParams &p, const uint32_t *cand, OffOf off_of,
+                                           uint32_t cnt, uint64_t (&F)[KPL], bool forgot) {
+  constexpr bool kRoomy = M::roomy(KPL);
+  const uint32_t l = lane_id();
+  typename M::Batch b;
+  m.issue(p.pages, off_of(l), b);
+  uint32_t c0 = 0;
+  for (; c0 + kWave < cnt; c0 += kWave) {
+    const uint32_t d = m.template dist_and_issue<kRoomy>(p.pages, off_of(c0 + kWave + l), b);
+    merge_keys<KPL, false>(F, ((uint64_t)d << 32) | ((uint64_t)cand[c0 + l] << 1), forgot, p.L);
   }
-  if constexpr (NCH > 2) merge_keys<KPL>(F, m.gather_key(A, 2 * kWave, cnt), forgot, p.L);
-  if constexpr (NCH > 3) merge_keys<KPL>(F, m.gather_key(B, 3 * kWave, cnt), forgot, p.L);
+  const uint32_t d = m.template dist<kRoomy>(b);
+  const uint64_t key = ((uint64_t)d << 32) | ((uint64_t)cand[c0 + l] << 1);
+  merge_keys<KPL, false>(F, c0 + l < cnt ? key : kInfKey, forgot, p.L);
 }
 
-// Waves per SIMD from the distance policy (M::kWavesPerSimd: 4 for uint8
-// rows up to 128 bytes, with an 8 KB visited table; 1 for gathered 96-d
-// float32 rows, which keep two batches of whole vectors in registers; 2
-// otherwise): one wave's gathers overlap the others' filtering and merging.  The grid is as large as the chip holds at
+// The same with two batches in flight (policies with one wave per SIMD, whose
+// gathers nothing else would overlap): NCH batches, a fixed schedule each.
+template <int NCH, int KPL, class M, class OffOf>
+__device__ __forceinline__ void eval_lines2(const M &m, const ResidentParams &p, const uint32_t *cand, OffOf off_of,
+                                            uint32_t cnt, uint64_t (&F)[KPL], bool forgot) {
+  constexpr bool kRoomy = M::roomy(KPL);
+  const uint32_t l = lane_id();
+  typename M::Batch A, B;
+  auto merge = [&](uint32_t c0, uint32_t d) {
+    const uint64_t key = ((uint64_t)d << 32) | ((uint64_t)cand[c0 + l] << 1);
+    merge_keys<KPL, false>(F, c0 + l < cnt ? key : kInfKey, forgot, p.L);
+  };
+  m.issue(p.pages, off_of(l), A);
+  if constexpr (NCH > 1) m.issue(p.pages, off_of(kWave + l), B);
+  if constexpr (NCH > 2) merge(0, m.template dist_and_issue<kRoomy>(p.pages, off_of(2 * kWave + l), A));
+  else merge(0, m.template dist<kRoomy>(A));
+  if constexpr (NCH > 3) merge(kWave, m.template dist_and_issue<kRoomy>(p.pages, off_of(3 * kWave + l), B));
+  else if constexpr (NCH > 1) merge(kWave, m.template dist<kRoomy>(B));
+  if constexpr (NCH > 2) merge(2 * kWave, m.template dist<kRoomy>(A));
+  if constexpr (NCH > 3) merge(3 * kWave, m.template dist<kRoomy>(B));
+}
+
+// Waves per SIMD and the visited table from the distance policy
+// (M::waves_per_simd, M::ht_log2): one wave's gathers overlap the others'
+// filtering and merging.  The grid is as large as the chip holds at
 // once; workgroup b starts with query b and then takes the next unclaimed
 // query from a global counter, so the XCDs and CUs that finish early take
 // more queries and the batch ends when the last queries end, wherever they
 // run.
 template <int KPL, class M, class HT, bool N2S>
-__global__ __launch_bounds__(kWave, M::kWavesPerSimd) void search_resident(ResidentParams p) {
-  constexpr int kChunks = M::kChunks;
-  constexpr int kBatch = M::kBatch;
+__global__ __launch_bounds__(kWave, M::waves_per_simd(KPL)) void search_resident(ResidentParams p) {
   constexpr int kIdsPerLane = kCandCap / kWave;
 
   __shared__ __align__(16) uint32_t ht[HT::kWords];
   __shared__ __align__(16) uint32_t cand[kCandCap];
-  __shared__ uint32_t beam[kMaxW];
+  __shared__ uint32_t beam[KPL * kWave];  // W <= L
+  // candidates' byte offsets, worked out as they are compacted: the placement
+  // is then looked up beside the filter, for all ids of a group at once
+  constexpr bool kOffsets = M::kOffsets || (N2S && !M::kLocators && (M::kStream || M::kGathered));
+  __shared__ __align__(16) uint64_t coff[kOffsets ? kCandCap : 1];
   __shared__ __align__(16) uint32_t qbuf[M::kQueryWords];
+  __shared__ __align__(16) uint32_t stage[M::stage_words(KPL) ? M::stage_words(KPL) : 1];
 
   const int l = lane_id();
   const uint32_t beams_per_group = min(kCandCap / p.R, (uint32_t)kWave);
   const uint32_t entry_word = M::cand_word(p.geom, p.entry);
+  const uint64_t entry_off = vec_offset(p.geom, slot_ct<N2S>(p.geom, p.entry));
 
   unsigned long long n_eval = 0, n_reeval = 0, n_exp = 0, n_iter = 0;
 
@@ -120,6 +144,7 @@ __global__ __launch_bounds__(kWave, M::kWavesPerSimd) void search_resident(Resid
     HT::clear(ht);
     M m;
     m.load_query(p.queries, qi, p.D, qbuf);
+    m.set_stage(stage);
     __syncthreads();
 
     uint32_t ht_used = 0;
@@ -130,7 +155,7 @@ __global__ __launch_bounds__(kWave, M::kWavesPerSimd) void search_resident(Resid
 #pragma unroll
     for (int r = 0; r < KPL; ++r) F[r] = kInfKey;
     {
-      const uint32_t d = m.dist_one(p.pages + vec_offset(p.geom, slot_ct<N2S>(p.geom, p.entry)));
+      const uint32_t d = m.dist_one(p.pages, entry_off);
       if (l == 0) {
         F[0] = ((uint64_t)d << 32) | ((uint64_t)p.entry << 1);
         bool rec;
@@ -230,6 +255,11 @@ __global__ __launch_bounds__(kWave, M::kWavesPerSimd) void search_resident(Resid
             valid[t] = (uint32_t)(t * kWave + l) < nslots && slot_j[t] < deg && ids[t] < p.n;
           }
         }
+        [[maybe_unused]] uint32_t slot[kIdsPerLane];
+        if constexpr (kOffsets) {
+#pragma unroll
+          for (int t = 0; t < kIdsPerLane; ++t) slot[t] = slot_ct<N2S>(p.geom, valid[t] ? ids[t] : p.entry);
+        }
         // ---- filter through the visited table, compact the new ids ------------
         bool isnew[kIdsPerLane], recorded[kIdsPerLane];
         HT::template test_and_set_n<kIdsPerLane>(ht, ids, valid, ht_used < HT::kLimit, isnew, recorded);
@@ -238,48 +268,57 @@ __global__ __launch_bounds__(kWave, M::kWavesPerSimd) void search_resident(Resid
         for (int t = 0; t < kIdsPerLane; ++t) {
           const uint64_t mnew = ballot(isnew[t]);
           const uint64_t mrec = ballot(recorded[t]);
-          if (isnew[t]) cand[M::cand_pos(cnt + lanes_below(mnew))] = M::cand_word(p.geom, ids[t]);
+          if (isnew[t]) {
+            const uint32_t at = M::cand_pos(cnt + lanes_below(mnew));
+            cand[at] = M::cand_word(p.geom, ids[t]);
+            if constexpr (kOffsets) coff[at] = vec_offset(p.geom, slot[t]);
+          }
           cnt += (uint32_t)__popcll(mnew);
           ht_used += (uint32_t)__popcll(mrec);
           const uint32_t lost = (uint32_t)__popcll(mnew & ~mrec);
           n_reeval += lost;
           forgot |= lost != 0;
         }
-        M::pad_round(cand, cnt, entry_word);
+        M::pad_round(cand, coff, cnt, entry_word, entry_off);
         __syncthreads();
         n_eval += cnt;
 
         // ---- evaluate and merge -----------------------------------------------
-        if constexpr (M::kLocators) {
+        if constexpr (M::kStream) {
           // chunks of 64 vectors, two in flight: the next chunk's gathers are
           // outstanding while this one is reduced and merged (a fixed schedule
           // per chunk count keeps every wait exact)
           static_assert(kCandCap == 4 * kWave, "at most four chunks");
           switch ((cnt + kWave - 1) / kWave) {
-            case 1: eval_chunks<1, KPL>(m, p, cand, cnt, F, forgot); break;
-            case 2: eval_chunks<2, KPL>(m, p, cand, cnt, F, forgot); break;
-            case 3: eval_chunks<3, KPL>(m, p, cand, cnt, F, forgot); break;
-            case 4: eval_chunks<4, KPL>(m, p, cand, cnt, F, forgot); break;
+            case 1: eval_chunks<1, KPL>(m, p, cand, coff, cnt, F, forgot); break;
+            case 2: eval_chunks<2, KPL>(m, p, cand, coff, cnt, F, forgot); break;
+            case 3: eval_chunks<3, KPL>(m, p, cand, coff, cnt, F, forgot); break;
+            case 4: eval_chunks<4, KPL>(m, p, cand, coff, cnt, F, forgot); break;
             default: break;
           }
-        } else if constexpr (M::kGathered && !N2S) {
-          // float32 line gather, two batches of 64 in flight (with a
-          // placement permutation the next batch's slot loads would wait on
-          // the older batch's loads, so that case takes the plain loop)
-          switch ((cnt + kWave - 1) / kWave) {
-            case 1: eval_gathered<1, KPL, N2S>(m, p, cand, cnt, F, forgot); break;
-            case 2: eval_gathered<2, KPL, N2S>(m, p, cand, cnt, F, forgot); break;
-            case 3: eval_gathered<3, KPL, N2S>(m, p, cand, cnt, F, forgot); break;
-            case 4: eval_gathered<4, KPL, N2S>(m, p, cand, cnt, F, forgot); break;
-            default: break;
+        } else if constexpr (M::kGathered) {
+          auto off_of = [&](uint32_t i) {
+            if constexpr (kOffsets) return i < cnt ? coff[i] : entry_off;
+            else return vec_offset(p.geom, i < cnt ? cand[i] : p.entry);
+          };
+          if constexpr (M::two_batches(KPL)) {
+            switch ((cnt + kWave - 1) / kWave) {
+              case 1: eval_lines2<1, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
+              case 2: eval_lines2<2, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
+              case 3: eval_lines2<3, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
+              case 4: eval_lines2<4, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
+              default: break;
+            }
+          } else if (cnt != 0) {
+            eval_lines<KPL>(m, p, cand, off_of, cnt, F, forgot);
           }
         } else {
           // batches of kBatch vectors, one round trip each
-          for (uint32_t c0 = 0; c0 < cnt; c0 += kBatch) {
-            uint64_t key[kChunks];
+          for (uint32_t c0 = 0; c0 < cnt; c0 += M::kBatch) {
+            uint64_t key[M::kChunks];
             m.template resident_keys<N2S>(p.pages, p.geom, cand, c0, cnt, p.entry, key);
 #pragma unroll
-            for (int c = 0; c < kChunks; ++c) merge_keys<KPL>(F, key[c], forgot, p.L);
+            for (int c = 0; c < M::kChunks; ++c) merge_keys<KPL>(F, key[c], forgot, p.L);
           }
         }
         __syncthreads();
