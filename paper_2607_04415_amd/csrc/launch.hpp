@@ -9,6 +9,7 @@
 
 #include "search_paged.hpp"
 #include "search_resident.hpp"
+#include "search_team.hpp"
 
 namespace gorio {
 
@@ -70,9 +71,51 @@ hipError_t resident_t(const ResidentParams &p, int grid, hipStream_t s) {
   return hipErrorInvalidValue;  // not reached: the caller checks p.n
 }
 
+// Small batches: a team of waves per query while the chip holds all of them at
+// once; `done` tells whether the batch was launched.  Past that the teams'
+// idle waves cost more than the shorter chain saves (1M x 128 uint8, L=64:
+// 1,024 queries 140 us with teams, 197 with a wave each; 2,048 246 and 259;
+// L=128, where 512 teams fit: 512 queries 287 and 391 us, 1,024 415 and 394;
+// 300k x 128 float32, L=64, 512 fit: 178 and 272, 1,024 322 and 297).
+template <int KPL, class M, int T>
+hipError_t team_t(const ResidentParams &p, hipStream_t s, bool &done) {
+  constexpr auto Kernel = search_team<KPL, M, VisitedLds16<M::team_ht_log2(KPL)>, T>;
+  static int slots = 0;  // per kernel
+  if (slots == 0) {
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(Kernel), T * kWave, 0);
+    if (e != hipSuccess) return e;
+    slots = std::max(1, cus * per_cu);
+  }
+  done = p.nq <= (uint32_t)slots && p.n <= VisitedLds16<M::team_ht_log2(KPL)>::kMaxId;
+  if (!done) return hipSuccess;
+  Kernel<<<p.nq, T * kWave, 0, s>>>(p);
+  return hipGetLastError();
+}
+
+// frontier slots per lane (L <= 64 KPL)
+template <class M>
+hipError_t team(const ResidentParams &p, hipStream_t s, bool &done) {
+  if (p.L <= 64) {
+    // beams of up to 128 ids keep two waves busy
+    if (p.W * p.R <= 2 * kWave) return team_t<1, M, 2>(p, s, done);
+    return team_t<1, M, M::team_waves(1)>(p, s, done);
+  }
+  if (p.L <= 128) return team_t<2, M, M::team_waves(2)>(p, s, done);
+  return team_t<4, M, M::team_waves(4)>(p, s, done);
+}
+
 // frontier slots per lane (L <= 64 KPL) and node_to_slot presence
 template <class M>
 hipError_t resident(const ResidentParams &p, int grid, hipStream_t s) {
+  if constexpr (M::kStream || M::kGathered) {
+    bool done = false;
+    const hipError_t e = team<M>(p, s, done);
+    if (done || e != hipSuccess) return e;
+  }
   if constexpr (M::kLocators) {  // identity placement only
     if (p.L <= 64) return resident_t<1, M, false>(p, grid, s);
     if (p.L <= 128) return resident_t<2, M, false>(p, grid, s);
