@@ -96,6 +96,7 @@ __device__ __forceinline__ float score_margin(uint32_t D, float xx, float cmax2)
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The three least scores of a vector so far and the first two's centroids.
 struct Top3 {
@@ -141,15 +142,36 @@ __global__ __launch_bounds__(256, 2) void nearest_matrix(const T *v, uint64_t co
     const uint64_t i = base + n * 32 + col;
     const T *p = v + (i < count ? i : count - 1) * D;
     float xx = 0.0f;
+    const bool whole = D % 4 == 0;  // rows start on, and end with, whole fours
 #pragma unroll
-    for (int q = 0; q < DQ; ++q)
+    for (int q = 0; q < DQ; ++q) {
+      const uint32_t d0 = 8 * q + 4 * h;
+      float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (whole) {
+        if (d0 < D) {
+          if constexpr (sizeof(T) == 1) {
+            const uint32_t b = *reinterpret_cast<const uint32_t *>(p + d0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) f[t] = (float)((b >> (8 * t)) & 0xFFu);
+          } else {
+            const float4 b = *reinterpret_cast<const float4 *>(p + d0);
+            f[0] = b.x;
+            f[1] = b.y;
+            f[2] = b.z;
+            f[3] = b.w;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (d0 + t < D) f[t] = (float)p[d0 + t];
+      }
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const uint32_t d = 8 * q + 4 * h + t;
-        const float e = d < D ? (float)p[d] : 0.0f;
-        x[n][q][t] = e;
-        xx += e * e;
+        x[n][q][t] = f[t];
+        xx += f[t] * f[t];
       }
+    }
     xx += __shfl_xor(xx, 32);
     margin[n] = score_margin(D, xx, __uint_as_float(*most));
   }
@@ -158,8 +180,8 @@ __global__ __launch_bounds__(256, 2) void nearest_matrix(const T *v, uint64_t co
 #pragma unroll
   for (int n = 0; n < NT; ++n) top[n] = {inf, inf, inf, 0, 0};
   const uint32_t tiles = Kp / 32;
-  const float4 *src = reinterpret_cast<const float4 *>(rows);
-  float4 st[kPer];
+  const f32x4 *src = reinterpret_cast<const f32x4 *>(rows);
+  f32x4 st[kPer];
   auto fetch = [&](uint32_t t) {
 #pragma unroll
     for (int j = 0; j < kPer; ++j) st[j] = src[(uint64_t)t * (32 * DP / 4) + j * 256 + threadIdx.x];
@@ -168,7 +190,7 @@ __global__ __launch_bounds__(256, 2) void nearest_matrix(const T *v, uint64_t co
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const int e = j * 256 + threadIdx.x, r = e / (DP / 4), q = e % (DP / 4);
-      *reinterpret_cast<float4 *>(&tile[t & 1][r * kRow + 4 * q]) = st[j];
+      *reinterpret_cast<f32x4 *>(&tile[t & 1][r * kRow + 4 * q]) = st[j];
     }
     if (threadIdx.x < 32) tcc[t & 1][threadIdx.x] = cc[t * 32 + threadIdx.x];
   };
