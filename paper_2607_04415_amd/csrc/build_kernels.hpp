@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void column_sums_u8(const uint8_t *x, uint32_t
 // (1M x 96: 65.4 ms with one thread per column and eight loads in flight), so
 // the runs of kSumRun rows are worked out side by side (ordered_sum.hpp): the
 // rows are read twice at memory speed, and the chain that is left has one step
-// per run (1M x 96: see launch_column_sums_f32).
+// per run (1M x 96: 0.19 ms for the two reads and the starts, 0.57 ms for the chain).
 __global__ __launch_bounds__(256) void sum_outlines_f32(const float *x, uint32_t n, uint32_t D, uint32_t runs,
                                                         RunOutline *out) {
   const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;

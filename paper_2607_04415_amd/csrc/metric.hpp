@@ -272,9 +272,12 @@ struct MetricU8 {
 // unit before it has already, so nothing past the row is read and every
 // dimension counts once.  Candidates' byte offsets are worked out once, when
 // they are compacted, and read back from LDS; two chunks of 64 vectors are in
-// flight.  (Dword loads with a bound check on each, and the placement looked
-// up between compaction and gather: 300k x 100, contiguous, placed, 5,000
-// queries 620 us a launch.)
+// flight.  Bound by the lines read (a 100-byte row in a 296-byte record lies
+// on 1.8 of them).  Against dword loads with a bound check on each, and the
+// placement looked up between compaction and gather (300k rows, 5,000 queries,
+// L=64, us a launch): 100 bytes, contiguous, placed 620 -> 513; whole calls:
+// 128 placed 552 -> 413, 128 contiguous 635 -> 564, 200 bytes 1,319 -> 743, 256
+// placed at L=128 2,089 -> 704.
 // ---------------------------------------------------------------------------
 template <int NU, bool EXACT>
 struct MetricU8Rows {
@@ -460,7 +463,9 @@ struct MetricF32 {  // paged kernels: one lane per candidate, records in the pag
 // vectors at a time, so that each lane gets the line of its own vector for the
 // sequential sum (no VALU work moves them).  The lines of one batch of 64
 // vectors are in flight at any time: as a line is taken out of its registers
-// the same line of the next batch is read into them.
+// the same line of the next batch is read into them.  Bound by random line
+// reads: 300k x 128, R=32, L=64, 5,000 queries 2.79 ms with a lane per vector
+// (1.8 TB/s), 0.81 ms now (6.5 TB/s; such reads reach 6.8); 256-d 3.78 -> 1.27.
 // EXACT: every line is whole (D = 32 J); for the 16-bit visited tables only.
 template <int J, bool EXACT = false>
 struct MetricF32Lines {

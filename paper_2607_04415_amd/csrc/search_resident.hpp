@@ -13,11 +13,11 @@
 //             group's lists while the current one is filtered and evaluated;
 //   filter  - ids already in the visited filter are dropped (LDS atomics),
 //             the rest compacted into an LDS candidate list;
-//   evaluate- one round trip gathers a batch of candidate vectors; the
-//             distance policy (metric.hpp) turns them into keys: uint8 with
-//             8 lanes per 128-B vector and v_dot4_u32_u8, float32 with one
-//             lane per vector (96-d rows read 8 lanes per vector by lines,
-//             then transposed in registers) and the sequential rounded sum;
+//   evaluate- one round trip gathers a batch of candidate vectors by whole
+//             lines, 8 lanes per vector; the distance policy (metric.hpp)
+//             turns them into keys: uint8 with v_dot4_u32_u8, float32 with one
+//             lane per vector (the blocks reach it through LDS) and the
+//             sequential rounded sum;
 //   merge   - only keys below F's L-th key can enter: a few are inserted by
 //             rank (ballot + DPP shift), many are bitonic-sorted per 64-lane
 //             chunk and bitonic-merged into F.
