@@ -35,6 +35,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <mutex>
 #include <thread>
 #include <vector>
 
@@ -115,6 +116,7 @@ int main(int argc, char **argv) {
   c.mq_tail = &mq_tail;
 
   std::atomic<uint64_t> next_query{0}, done_queries{0}, mq_head{0};
+  std::mutex mq_reader;
   std::atomic<uint64_t> hits{0}, joins{0}, misses{0}, noslot{0}, served{0}, bad{0}, completed{0};
   std::atomic<bool> stop{false}, stalled{false};
   std::atomic<int64_t> last_progress{clk::now().time_since_epoch().count()};
@@ -207,20 +209,27 @@ int main(int argc, char **argv) {
   auto fill_side = [&](int f) {
     uint64_t rng = splitmix64(seed + 1000 + f);
     while (!stop.load()) {
-      const uint64_t h = mq_head.load();
-      if (h >= __atomic_load_n(&mq_tail, __ATOMIC_SEQ_CST)) {
+      // One thread at a time takes a descriptor and clears its entry, as the
+      // proxy (the ring's one reader) does: a thread held up between the two
+      // while the others went once round the ring would clear a later one.
+      unsigned long long e = 0;
+      {
+        std::lock_guard<std::mutex> taking(mq_reader);
+        const uint64_t h = mq_head.load();
+        if (h < __atomic_load_n(&mq_tail, __ATOMIC_SEQ_CST)) {
+          while ((e = __atomic_load_n(&mq[h & (ring - 1)], __ATOMIC_SEQ_CST)) == 0) {
+            if (stop.load()) return;
+            std::this_thread::yield();
+          }
+          __atomic_store_n(&mq[h & (ring - 1)], 0ull, __ATOMIC_SEQ_CST);
+          mq_head.store(h + 1);
+        }
+      }
+      if (e == 0) {
         if (done_queries.load() >= queries) break;
         std::this_thread::yield();
         continue;
       }
-      uint64_t expect = h;
-      if (!mq_head.compare_exchange_strong(expect, h + 1)) continue;
-      unsigned long long e;
-      while ((e = __atomic_load_n(&mq[h & (ring - 1)], __ATOMIC_SEQ_CST)) == 0) {
-        if (stop.load()) return;
-        std::this_thread::yield();
-      }
-      __atomic_store_n(&mq[h & (ring - 1)], 0ull, __ATOMIC_SEQ_CST);
       const uint32_t page = (uint32_t)(e >> 32) - 1u, s = (uint32_t)e;
       if (page >= pages || s >= slots) { bad.fetch_add(1); continue; }
       const uint64_t w = __atomic_load_n(&slot_word[s], __ATOMIC_SEQ_CST);
