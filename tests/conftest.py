@@ -45,6 +45,13 @@ def random_graph(rng, n, R, connected=True, sentinel_frac=0.0):
     return g
 
 
+def wave_per_query_batch(torch):
+    """A batch that no team kernel takes: teams have at least two waves, a CU
+    holds at most 32, and a batch goes to teams only while all of them are
+    held at once."""
+    return torch.cuda.get_device_properties(0).multi_processor_count * 16 + 1
+
+
 def brute_force(x, q, k, dtype="u8"):
     """Exact top-k by (squared L2, id) with numpy; float64 for float32 data."""
     if dtype == "u8":

@@ -19,7 +19,7 @@ import numpy as np
 import pytest
 
 import paper_2607_04415_amd as g
-from conftest import NO_EDGE, random_graph
+from conftest import NO_EDGE, random_graph, wave_per_query_batch
 from workload import IndexSpec, QuerySpec, WORKLOADS, index_arrays, query_array
 
 pytestmark = pytest.mark.gpu
@@ -53,7 +53,8 @@ def f32_acceptance(gi, gd, oids, od, rel=1e-5, overlap=0.999):
     assert total == 0 or common / total >= overlap
 
 
-def check_parity(orc, torch, x, graph, q, k, L, W, layout=None, entry=None, counts=True):
+def check_parity(orc, torch, x, graph, q, k, L, W, layout=None, entry=None, counts=True, batch=None):
+    """batch: search that many queries, q over and over."""
     layout = layout or {}
     ix = g.Index(x, graph, entry=entry, **layout)
     e = ix.info["entry"]
@@ -61,6 +62,9 @@ def check_parity(orc, torch, x, graph, q, k, L, W, layout=None, entry=None, coun
         assert e == orc.medoid(x)
     okw = {kk: v for kk, v in layout.items() if v is not None and not (np.isscalar(v) and v == 0)}
     oids, od, oc, _ = orc.pack(x, graph, **okw).search(q, k, L, W, e, threads=8)
+    if batch is not None:
+        rows = np.arange(batch) % len(q)
+        q, oids, od, oc = q[rows], oids[rows], od[rows], oc[rows]
     gi, gd, st = run_gpu(torch, ix, q, k, L, W)
     if gd.dtype == np.float32:
         f32_acceptance(gi, gd, oids, od)
@@ -170,40 +174,59 @@ def test_unreachable_and_padding(orc, torch_dev):
     assert (gi[:, 5:] == NO_EDGE).all() and (gd[:, 5:] == 2 ** 31 - 1).all()
 
 
-def test_visited_filter_overflow_still_exact(orc, torch_dev):
+# every policy's table, by teams (a small batch) and by a wave per query
+OVERFLOWS = [("u8", 128), ("u8", 16), ("u8", 100), ("u8", 200), ("u8", 260), ("f32", 3), ("f32", 32), ("f32", 50),
+             ("f32", 96), ("f32", 128), ("f32", 150)]
+
+
+@pytest.mark.parametrize("waves", ["teams", "wave-per-query"])
+@pytest.mark.parametrize("dtype,D", OVERFLOWS)
+def test_visited_filter_overflow_still_exact(orc, torch_dev, dtype, D, waves):
     """A search that outgrows the visited table forgets nodes: re-evaluations
-    happen, results and expansion counts do not change."""
-    spec = IndexSpec(n=60000, D=64, dtype="u8", clusters=8, sigma=20.0, r_near=32, r_rand=32, seed=9)
-    a = index_arrays(spec, use_cache=False)
-    q = query_array(spec, QuerySpec(64, 10))
-    _, st = check_parity(orc, torch_dev, a["x"], a["graph"], q, 10, 256, 8)
+    happen, results and expansion counts do not change.  About 16,500 ids are
+    met; the largest table records 14,336."""
+    rng = np.random.default_rng(9 + D)
+    n, R = 200_000, 64
+    if dtype == "u8":
+        x, q = (rng.integers(0, 256, (m, D), dtype=np.uint8) for m in (n, 48))
+    else:
+        x, q = (rng.standard_normal((m, D), dtype=np.float32) for m in (n, 48))
+    graph = rng.integers(0, n, (n, R), dtype=np.uint32)
+    batch = wave_per_query_batch(torch_dev) if waves == "wave-per-query" else None
+    for L, W in ((128, 8), (256, 8)):
+        ix, st = check_parity(orc, torch_dev, x, graph, q, 10, L, W, entry=7, batch=batch)
+        ix.close()
     assert st["reevaluations"] > 0, "the test did not exercise the overflow path"
 
 
-def _home_bucket_u8(ids, log2=12):
-    """Home bucket of each id in the resident uint8 kernel's 16-bit visited
-    table with 2^log2 half-words: the top log2 - 3 bits of
-    h = (id * 0x3779B1) mod 2^(log2 + 11) (the hash's 24-bit multiplier)."""
+def _home_bucket(ids, log2):
+    """Home bucket of each id in a 16-bit visited table with 2^log2 half-words:
+    the top log2 - 3 bits of h = (id * 0x3779B1) mod 2^(log2 + 11) (the
+    hash's 24-bit multiplier)."""
     h = (ids.astype(np.uint64) * 0x3779B1) % (1 << (log2 + 11))
     return (h >> 14).astype(np.int64)
 
 
-@pytest.mark.parametrize("vectors_first", [False, True])
-def test_visited_filter_bucket_collisions(orc, torch_dev, vectors_first):
+# the table's size follows the kernel: vectors first, 128 bytes, a wave per
+# query and L <= 64 has 2^12 half-words; teams and other rows have 2^13
+@pytest.mark.parametrize("vectors_first,waves,log2", [(True, "wave-per-query", 12), (True, "teams", 13),
+                                                      (False, "wave-per-query", 13), (False, "teams", 13)])
+def test_visited_filter_bucket_collisions(orc, torch_dev, vectors_first, waves, log2):
     """Adjacency lists built to collide in the visited table: 64 neighbours
     that share one home bucket (seven slots fill, the rest take the next
     bucket or go unrecorded), lists of a few ids repeated many times (lanes
     holding the same id), and beams whose lists overlap."""
     rng = np.random.default_rng(77)
-    n, D, R = 50000, 128, 64
+    n, D, R = 100_000, 128, 64
     x = rng.integers(0, 256, (n, D), dtype=np.uint8)
     graph = rng.integers(0, n, (n, R), dtype=np.uint32)
     graph[:, 0] = (np.arange(n, dtype=np.uint32) + 1) % n
-    home = _home_bucket_u8(np.arange(n))
-    buckets = np.bincount(home, minlength=512)
+    nb = 1 << (log2 - 3)
+    home = _home_bucket(np.arange(n), log2)
+    buckets = np.bincount(home, minlength=nb)
     b = int(np.argmax(buckets))
     same = np.flatnonzero(home == b)
-    nxt = np.flatnonzero(home == (b + 1) % 512)
+    nxt = np.flatnonzero(home == (b + 1) % nb)
     assert len(same) >= 64 and len(nxt) >= 64
     graph[0] = rng.permutation(same)[:64]                       # one bucket, 64 ids
     for j, v in enumerate(graph[0][:8]):                        # their lists: more of it
@@ -213,20 +236,33 @@ def test_visited_filter_bucket_collisions(orc, torch_dev, vectors_first):
     for v in graph[0][16:24]:                                   # overlapping lists
         graph[v] = graph[graph[0][0]]
     q = rng.integers(0, 256, (96, D), dtype=np.uint8)
+    batch = wave_per_query_batch(torch_dev) if waves == "wave-per-query" else None
     _, st = check_parity(orc, torch_dev, x, graph, q, 10, 64, 4, entry=0,
-                         layout=dict(vectors_first=vectors_first))
+                         layout=dict(vectors_first=vectors_first), batch=batch)
+    # the entry's list alone overfills its two buckets: 14 of 64 ids find a slot
+    assert st["reevaluations"] >= 50 * (batch or len(q)), "the lists did not collide in this kernel's table"
 
 
-def test_more_than_2_24_nodes_uses_the_32bit_table(orc, torch_dev):
+@pytest.mark.parametrize("dtype,D,Ls", [("u8", 4, (64,)), ("u8", 36, (64, 100, 200)), ("f32", 1, (64,)),
+                                        ("f32", 32, (64, 100, 200))])
+def test_more_than_2_24_nodes_uses_the_32bit_table(orc, torch_dev, dtype, D, Ls):
     """Above 2^24 nodes the resident kernel's 16-bit visited table cannot hold
     every id; the 32-bit table takes over and results stay exact."""
     rng = np.random.default_rng(31)
-    n, D, R = (1 << 24) + 4099, 4, 4
-    x = rng.integers(0, 256, (n, D), dtype=np.uint8)
+    n, R = (1 << 24) + 4099, 4
+    if dtype == "u8":
+        x, q = (rng.integers(0, 256, (m, D), dtype=np.uint8) for m in (n, 64))
+    else:
+        x, q = (rng.random((m, D), dtype=np.float32) for m in (n, 64))
     graph = rng.integers(0, n, (n, R), dtype=np.uint32)
     graph[:, 0] = (np.arange(n, dtype=np.uint64) * 2654435761 % n).astype(np.uint32)  # long jumps
-    q = rng.integers(0, 256, (64, D), dtype=np.uint8)
-    check_parity(orc, torch_dev, x, graph, q, 10, 64, 4, entry=n - 1)
+    ix, packed = g.Index(x, graph, entry=n - 1), orc.pack(x, graph)
+    for L in Ls:
+        oids, od, oc, _ = packed.search(q, 10, L, 4, n - 1, threads=8)
+        gi, gd, st = run_gpu(torch_dev, ix, q, 10, L, 4)
+        assert np.array_equal(gi, oids) and np.array_equal(gd.view(np.uint32), od.view(np.uint32)), L
+        assert st["expansions"] == int(oc["expansions"].sum()) and st["evaluations"] == int(oc["evaluations"].sum())
+    ix.close()
 
 
 def test_single_node_and_widest_rows(orc, torch_dev):
@@ -348,14 +384,6 @@ def test_f32_ties_zero_distance_and_padding(orc, torch_dev):
     ix, _ = check_parity(orc, torch_dev, x2, g2, x2[:3], 8, 16, 2, entry=0)
     gi, gd, _ = run_gpu(torch_dev, ix, x2[:3], 8, 16, 2)
     assert (gi[:, 5:] == NO_EDGE).all() and np.isposinf(gd[:, 5:]).all()
-
-
-def test_f32_visited_filter_overflow_still_exact(orc, torch_dev):
-    spec = IndexSpec(n=60000, D=16, dtype="f32", clusters=8, sigma=0.05, r_near=32, r_rand=32, seed=25)
-    a = index_arrays(spec, use_cache=False)
-    q = query_array(spec, QuerySpec(48, 26))
-    _, st = check_parity(orc, torch_dev, a["x"], a["graph"], q, 10, 256, 8)
-    assert st["reevaluations"] > 0, "the test did not exercise the overflow path"
 
 
 def test_entry_rule_matches_oracle_f32(orc, torch_dev):

@@ -5,6 +5,8 @@ bit, ids and distances.  Lengths are the edges of the 16-byte units and
 import numpy as np
 import pytest
 
+from conftest import wave_per_query_batch
+
 pytestmark = pytest.mark.gpu
 
 N = 700
@@ -23,7 +25,8 @@ def make(dtype, D, R, seed):
     return x, q, graph
 
 
-def check(dtype, D, R, k, L, W, layout, placed, counts=(1, 40, 1500)):
+def check(dtype, D, R, k, L, W, layout, placed, counts=(1, 40, None)):
+    """counts: batch sizes; None is one that runs a wave per query."""
     import torch
     assert torch.cuda.is_available()   # before the library: both then share one HIP runtime
     import paper_2607_04415_amd as g
@@ -32,13 +35,13 @@ def check(dtype, D, R, k, L, W, layout, placed, counts=(1, 40, 1500)):
     n2s = np.random.default_rng(D).permutation(N).astype(np.uint32) if placed else None
     ix = g.Index(x, graph, node_to_slot=n2s, vectors_first=layout == "vectors")
     orc = load()
-    oids, od, oc, _ = orc.pack(x, graph).search(q, k, L, W, ix.info["entry"])
-    for nq in counts:   # up to 40: teams; 1,500: more than any policy's teams
-        ids, dists, st = ix.search(torch.from_numpy(q[:nq]).cuda(), k, L, W)
-        assert np.array_equal(ids.cpu().numpy().view(np.uint32), oids[:nq]), (nq, "ids")
-        assert np.array_equal(dists.cpu().numpy().view(np.uint32), od[:nq].view(np.uint32)), (nq, "distances")
-        assert st["expansions"] == int(oc["expansions"][:nq].sum())
-
+    oids, od, oc, _ = orc.pack(x, graph).search(q, k, L, W, ix.info["entry"], threads=8)
+    for nq in counts:
+        rows = np.arange(nq or wave_per_query_batch(torch)) % len(q)
+        ids, dists, st = ix.search(torch.from_numpy(q[rows]).cuda(), k, L, W)
+        assert np.array_equal(ids.cpu().numpy().view(np.uint32), oids[rows]), (nq, "ids")
+        assert np.array_equal(dists.cpu().numpy().view(np.uint32), od[rows].view(np.uint32)), (nq, "distances")
+        assert st["expansions"] == int(oc["expansions"][rows].sum())
     ix.close()
 
 
@@ -61,4 +64,15 @@ def test_f32_rows(D, layout, placed):
 @pytest.mark.parametrize("R,k,L,W", [(64, 10, 64, 1), (64, 64, 64, 9), (65, 10, 65, 8), (1, 1, 128, 128), (96, 100, 128, 5),
                                      (256, 10, 129, 3), (33, 200, 256, 256), (12, 12, 12, 12)])
 def test_beams(dtype, D, R, k, L, W):
-    check(dtype, D, R, k, L, W, "vectors", False, counts=(3, 1500))
+    check(dtype, D, R, k, L, W, "vectors", False, counts=(3, 512, None))
+
+
+# a wave per query with two and four frontier registers: beams of two groups,
+# groups of up to four batches of 64, placed and not
+@pytest.mark.parametrize("layout,placed", [("vectors", False), ("vectors", True), ("contiguous", True)])
+@pytest.mark.parametrize("L", [100, 200])
+@pytest.mark.parametrize("dtype,D", [("u8", 16), ("u8", 64), ("u8", 128), ("u8", 200), ("u8", 300), ("f32", 5),
+                                     ("f32", 20), ("f32", 32), ("f32", 64), ("f32", 90), ("f32", 96), ("f32", 128),
+                                     ("f32", 150), ("f32", 256)])
+def test_long_frontiers(dtype, D, L, layout, placed):
+    check(dtype, D, 64, 50, L, 8, layout, placed, counts=(None,))
