@@ -63,11 +63,13 @@ hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s
 template <int KPL, class M, bool N2S>
 hipError_t resident_t(const ResidentParams &p, int grid, hipStream_t s) {
   using Small = VisitedLds16<M::ht_log2(KPL)>;
-  constexpr int kGrid = M::grid_waves_per_simd(KPL);
+  using Large = ResidentHtLarge;
   if (M::kSmallIds || p.n <= Small::kMaxId)
-    return launch_resident_grid<search_resident<KPL, M, Small, N2S>, kGrid>(p, grid, s);
+    return launch_resident_grid<search_resident<KPL, M, Small, N2S>, M::grid_waves_per_simd(KPL, Small::kWords)>(
+        p, grid, s);
   if constexpr (!M::kSmallIds)
-    return launch_resident_grid<search_resident<KPL, M, ResidentHtLarge, N2S>, kGrid>(p, grid, s);
+    return launch_resident_grid<search_resident<KPL, M, Large, N2S>, M::grid_waves_per_simd(KPL, Large::kWords)>(
+        p, grid, s);
   return hipErrorInvalidValue;  // not reached: the caller checks p.n
 }
 

@@ -50,8 +50,10 @@ struct MetricU8 {
   // frontiers meet more nodes than 4096 entries record (L=128, W=8, R=64: 80M
   // of 148M evaluations were repeats), and two waves per SIMD leave room for
   // 16 KB each.
-  __host__ __device__ static constexpr int waves_per_simd(int kpl) { return VDW <= 4 && kpl == 1 ? 4 : 2; }
-  __host__ __device__ static constexpr int grid_waves_per_simd(int) { return 2; }
+  __host__ __device__ static constexpr int waves_per_simd(int kpl, uint32_t) { return VDW <= 4 && kpl == 1 ? 4 : 2; }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int, uint32_t table_words) {
+    return table_words > 4096 ? 1 : 2;
+  }
   __host__ __device__ static constexpr int ht_log2(int kpl) { return VDW <= 4 && kpl == 1 ? 12 : 13; }
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;  // INT32_MAX
   static_assert(!LOC16 || (EXACT && VDW % 4 == 0), "locators address whole 16-byte units");
@@ -59,7 +61,7 @@ struct MetricU8 {
   static constexpr bool kSmallIds = false;
   static constexpr bool kStream = LOC16;    // chunks of 64, two in flight
   static constexpr bool kOffsets = false;   // candidates' byte offsets kept in LDS
-  __host__ __device__ static constexpr int stage_words(int) { return 0; }  // LDS of a wave for set_stage
+  __host__ __device__ static constexpr uint32_t stage_words(int, uint32_t) { return 0; }  // LDS of a wave for set_stage
   // search_team (locators): waves per query, per SIMD at least, visited table
   __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 ? 8 : 4; }
   __host__ __device__ static constexpr int team_per_simd() { return 2; }
@@ -283,13 +285,15 @@ template <int NU, bool EXACT>
 struct MetricU8Rows {
   static constexpr int kQueryWords = 1;
   // two waves per SIMD: 256 registers, 16 KB visited table
-  __host__ __device__ static constexpr int waves_per_simd(int) { return 2; }
-  __host__ __device__ static constexpr int grid_waves_per_simd(int) { return 2; }
+  __host__ __device__ static constexpr int waves_per_simd(int, uint32_t) { return 2; }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int, uint32_t table_words) {
+    return table_words > 4096 ? 1 : 2;
+  }
   __host__ __device__ static constexpr int ht_log2(int) { return 13; }
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;
   static constexpr bool kLocators = false, kGathered = false, kStream = true, kOffsets = true;
   static constexpr bool kSmallIds = false;
-  __host__ __device__ static constexpr int stage_words(int) { return 0; }
+  __host__ __device__ static constexpr uint32_t stage_words(int, uint32_t) { return 0; }
   __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 ? 8 : 4; }
   __host__ __device__ static constexpr int team_per_simd() { return 2; }
   __host__ __device__ static constexpr int team_ht_log2(int) { return 13; }
@@ -473,19 +477,23 @@ struct MetricF32Lines {
   static constexpr uint32_t kPadDist = 0x7F800000u;  // +inf
   // A line takes 32 registers: up to four lines, two waves per SIMD.  Long
   // frontiers meet more nodes than a 16 KB visited table records, and 32 KB
-  // leave room for one.
-  __host__ __device__ static constexpr int waves_per_simd(int kpl) { return J <= 4 && kpl == 1 ? 2 : 1; }
-  __host__ __device__ static constexpr int grid_waves_per_simd(int kpl) { return waves_per_simd(kpl); }
-  __host__ __device__ static constexpr int ht_log2(int kpl) { return waves_per_simd(kpl) == 2 ? 13 : 14; }
+  // (the 32-bit table too) leave room for one.
+  __host__ __device__ static constexpr int ht_log2(int kpl) { return J <= 4 && kpl == 1 ? 13 : 14; }
+  __host__ __device__ static constexpr int waves_per_simd(int, uint32_t table_words) {
+    return J <= 4 && table_words <= 4096 ? 2 : 1;
+  }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int kpl, uint32_t w) { return waves_per_simd(kpl, w); }
   // With one wave per SIMD nothing else covers the LDS passes and the sums, so
   // such a kernel is given room (`roomy`): 32 vectors per LDS pass, and the
   // compiler may overlap one line's sums with the next lines' passes and keep
   // the query in registers; for whole lines two batches are in flight (1M x
   // 96, L=128, W=8, 10k queries: 5.27 ms without any of it, 4.83 with the
-  // ragged line's tests, 4.18 now).
-  __host__ __device__ static constexpr bool roomy(int kpl) { return waves_per_simd(kpl) == 1 && J <= 4; }
-  __host__ __device__ static constexpr bool two_batches(int kpl) { return EXACT && kpl == 2; }
-  __host__ __device__ static constexpr int stage_words(int kpl) { return roomy(kpl) ? 1024 : 512; }
+  // ragged line's tests, 4.18 now).  Not with four frontier registers: there
+  // they take the registers the overlap needs (100k x 96, L=200, 5,000 queries:
+  // R=16 1,541 us with one batch and 1,672 with two, R=64 2,650 and 2,883).
+  __host__ __device__ static constexpr bool roomy(int kpl, uint32_t w) { return waves_per_simd(kpl, w) == 1 && J <= 4; }
+  __host__ __device__ static constexpr bool two_batches(int kpl, uint32_t w) { return EXACT && roomy(kpl, w) && kpl == 2; }
+  __host__ __device__ static constexpr uint32_t stage_words(int kpl, uint32_t w) { return roomy(kpl, w) ? 1024 : 512; }
   static constexpr bool kLocators = false, kStream = false, kOffsets = false, kGathered = true;
   static constexpr bool kSmallIds = EXACT;  // only indexes whose ids fit the 16-bit tables
 

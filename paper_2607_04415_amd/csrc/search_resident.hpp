@@ -69,48 +69,141 @@ __device__ __forceinline__ void eval_chunks(const M &m, const ResidentParams &p,
   if constexpr (NCH > 3) merge_keys<KPL>(F, m.chunk_key(p.geom, cand, 3 * kWave, cnt, B), forgot, p.L);
 }
 
-// Evaluates cnt > 0 compacted candidates with the float32 line gather, 64 at a
-// time, and merges their keys into F; off_of(i) is candidate i's byte offset.
-// The last batch has its own copy so that every batch before it issues the
-// same loads and the waits stay exact.
-template <int KPL, class M, class OffOf>
-__device__ __forceinline__ void eval_lines(const M &m, const ResidentParams &p, const uint32_t *cand, OffOf off_of,
-                                           uint32_t cnt, uint64_t (&F)[KPL], bool forgot) {
-  constexpr bool kRoomy = M::roomy(KPL);
+// A group's cnt compacted candidates, 64 at a time, as the float32 line gather
+// takes them: lane l's candidate of the batch t ahead (past the count: any
+// record, its key is dropped).
+//
+// In LDS, in words of their own.
+template <bool N2S>
+struct LdsCandidates {
+  const uint32_t *cand;
+  const uint64_t *off;  // byte offsets, with a placement
+  uint32_t cnt, entry;
+  uint64_t entry_off;
+  uint32_t first = 0;
+
+  __device__ __forceinline__ uint32_t id(int t) const { return cand[first + t * kWave + lane_id()]; }
+  __device__ __forceinline__ uint64_t offset(const PageGeom &geom, int t) const {
+    const uint32_t i = first + t * kWave + lane_id();
+    if constexpr (N2S) return i < cnt ? off[i] : entry_off;
+    else return vec_offset(geom, i < cnt ? cand[i] : entry);
+  }
+  __device__ __forceinline__ void next() { first += kWave; }
+};
+// In registers: their words in LDS are then the stage's, which the lines pass
+// through.
+template <bool N2S>
+struct LaneCandidates {
+  uint32_t ids[kCandCap / kWave];
+  uint32_t slot[N2S ? kCandCap / kWave : 1];  // identity placement: slot = id
+
+  __device__ __forceinline__ void read(const uint32_t *cand, const uint32_t *slots, uint32_t cnt, uint32_t entry,
+                                       uint32_t entry_slot) {
+#pragma unroll
+    for (int t = 0; t < kCandCap / kWave; ++t) {
+      if (t * kWave >= cnt) break;
+      const uint32_t i = t * kWave + lane_id();
+      ids[t] = i < cnt ? cand[i] : entry;
+      if constexpr (N2S) slot[t] = i < cnt ? slots[i] : entry_slot;
+    }
+  }
+  __device__ __forceinline__ uint32_t id(int t) const { return ids[t]; }
+  __device__ __forceinline__ uint64_t offset(const PageGeom &geom, int t) const {
+    if constexpr (N2S) return vec_offset(geom, slot[t]);
+    else return vec_offset(geom, ids[t]);
+  }
+  __device__ __forceinline__ void next() {
+#pragma unroll
+    for (int t = 0; t + 1 < kCandCap / kWave; ++t) {
+      ids[t] = ids[t + 1];
+      if constexpr (N2S) slot[t] = slot[t + 1];
+    }
+  }
+};
+
+// Evaluates cnt > 0 candidates with the float32 line gather, 64 at a time, and
+// merges their keys into F.  The last batch has its own copy so that every
+// batch before it issues the same loads and the waits stay exact.
+template <int KPL, class M, bool ROOMY, class Cands>
+__device__ __forceinline__ void eval_lines(const M &m, const ResidentParams &p, Cands &c, uint32_t cnt,
+                                           uint64_t (&F)[KPL], bool forgot) {
   const uint32_t l = lane_id();
   typename M::Batch b;
-  m.issue(p.pages, off_of(l), b);
+  m.issue(p.pages, c.offset(p.geom, 0), b);
   uint32_t c0 = 0;
   for (; c0 + kWave < cnt; c0 += kWave) {
-    const uint32_t d = m.template dist_and_issue<kRoomy>(p.pages, off_of(c0 + kWave + l), b);
-    merge_keys<KPL, false>(F, ((uint64_t)d << 32) | ((uint64_t)cand[c0 + l] << 1), forgot, p.L);
+    const uint32_t d = m.template dist_and_issue<ROOMY>(p.pages, c.offset(p.geom, 1), b);
+    merge_keys<KPL, false>(F, ((uint64_t)d << 32) | ((uint64_t)c.id(0) << 1), forgot, p.L);
+    c.next();
   }
-  const uint32_t d = m.template dist<kRoomy>(b);
-  const uint64_t key = ((uint64_t)d << 32) | ((uint64_t)cand[c0 + l] << 1);
+  const uint32_t d = m.template dist<ROOMY>(b);
+  const uint64_t key = ((uint64_t)d << 32) | ((uint64_t)c.id(0) << 1);
   merge_keys<KPL, false>(F, c0 + l < cnt ? key : kInfKey, forgot, p.L);
 }
 
 // The same with two batches in flight (policies with one wave per SIMD, whose
 // gathers nothing else would overlap): NCH batches, a fixed schedule each.
-template <int NCH, int KPL, class M, class OffOf>
-__device__ __forceinline__ void eval_lines2(const M &m, const ResidentParams &p, const uint32_t *cand, OffOf off_of,
-                                            uint32_t cnt, uint64_t (&F)[KPL], bool forgot) {
-  constexpr bool kRoomy = M::roomy(KPL);
+template <int NCH, int KPL, class M, bool ROOMY, class Cands>
+__device__ __forceinline__ void eval_lines2(const M &m, const ResidentParams &p, const Cands &c, uint32_t cnt,
+                                            uint64_t (&F)[KPL], bool forgot) {
   const uint32_t l = lane_id();
   typename M::Batch A, B;
-  auto merge = [&](uint32_t c0, uint32_t d) {
-    const uint64_t key = ((uint64_t)d << 32) | ((uint64_t)cand[c0 + l] << 1);
-    merge_keys<KPL, false>(F, c0 + l < cnt ? key : kInfKey, forgot, p.L);
+  auto merge = [&](int t, uint32_t d) {
+    const uint64_t key = ((uint64_t)d << 32) | ((uint64_t)c.id(t) << 1);
+    merge_keys<KPL, false>(F, t * kWave + l < cnt ? key : kInfKey, forgot, p.L);
   };
-  m.issue(p.pages, off_of(l), A);
-  if constexpr (NCH > 1) m.issue(p.pages, off_of(kWave + l), B);
-  if constexpr (NCH > 2) merge(0, m.template dist_and_issue<kRoomy>(p.pages, off_of(2 * kWave + l), A));
-  else merge(0, m.template dist<kRoomy>(A));
-  if constexpr (NCH > 3) merge(kWave, m.template dist_and_issue<kRoomy>(p.pages, off_of(3 * kWave + l), B));
-  else if constexpr (NCH > 1) merge(kWave, m.template dist<kRoomy>(B));
-  if constexpr (NCH > 2) merge(2 * kWave, m.template dist<kRoomy>(A));
-  if constexpr (NCH > 3) merge(3 * kWave, m.template dist<kRoomy>(B));
+  m.issue(p.pages, c.offset(p.geom, 0), A);
+  if constexpr (NCH > 1) m.issue(p.pages, c.offset(p.geom, 1), B);
+  if constexpr (NCH > 2) merge(0, m.template dist_and_issue<ROOMY>(p.pages, c.offset(p.geom, 2), A));
+  else merge(0, m.template dist<ROOMY>(A));
+  if constexpr (NCH > 3) merge(1, m.template dist_and_issue<ROOMY>(p.pages, c.offset(p.geom, 3), B));
+  else if constexpr (NCH > 1) merge(1, m.template dist<ROOMY>(B));
+  if constexpr (NCH > 2) merge(2, m.template dist<ROOMY>(A));
+  if constexpr (NCH > 3) merge(3, m.template dist<ROOMY>(B));
 }
+
+template <int KPL, class M, uint32_t TABLE_WORDS, class Cands>
+__device__ __forceinline__ void eval_group(const M &m, const ResidentParams &p, Cands &c, uint32_t cnt,
+                                           uint64_t (&F)[KPL], bool forgot) {
+  constexpr bool kRoomy = M::roomy(KPL, TABLE_WORDS);
+  if constexpr (M::two_batches(KPL, TABLE_WORDS)) {
+    switch ((cnt + kWave - 1) / kWave) {
+      case 1: eval_lines2<1, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
+      case 2: eval_lines2<2, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
+      case 3: eval_lines2<3, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
+      case 4: eval_lines2<4, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
+      default: break;
+    }
+  } else if (cnt != 0) {
+    eval_lines<KPL, M, kRoomy>(m, p, c, cnt, F, forgot);
+  }
+}
+
+// LDS of a search_resident workgroup.  launch_bounds cannot see it, so the sum
+// is held against the share of the waves that are meant to run: 160 KB over
+// four SIMDs.  The compacted candidates (ids, with a placement also byte
+// offsets) have words of their own; where that would cost a wave, the line
+// gather keeps ids and slots in the stage's words and takes them into
+// registers before the first line passes through (100k x 96, placed, 5,000
+// queries, L=200: 2,741 us with three workgroups per CU of 41 KB, 2,043 with
+// four; L=64, seven workgroups of 22 KB and eight: 1,097 and 1,062).  Where
+// they fit, their own words are the faster form (up to 2%).
+template <int KPL, class M, class HT, bool N2S>
+struct ResidentLds {
+  static constexpr int kCompiled = M::waves_per_simd(KPL, HT::kWords), kGrid = M::grid_waves_per_simd(KPL, HT::kWords);
+  static constexpr uint32_t kShare = 160 * 1024 / 4 / (kCompiled < kGrid ? kCompiled : kGrid);
+  static constexpr uint32_t kStageWords = M::stage_words(KPL, HT::kWords);
+  static constexpr bool kPlaced = M::kOffsets || (M::kGathered && N2S);
+  static constexpr uint32_t kOwnBytes = 4 * (kCandCap + (kPlaced ? 2 * kCandCap : 0));
+  // (a query kept in registers leaves its one word unused)
+  static constexpr uint32_t kOtherBytes =
+      4 * (HT::kWords + KPL * kWave + (M::kQueryWords > 1 ? M::kQueryWords : 0) + kStageWords);
+  static constexpr bool kInStage = M::kGathered && kOtherBytes + kOwnBytes > kShare;
+  static_assert(!kInStage || kStageWords >= 2 * kCandCap, "ids and slots fit the stage");
+  static constexpr bool kOffsets = kPlaced && !kInStage, kSlots = kPlaced && kInStage;
+  static constexpr uint32_t kBytes = kOtherBytes + (kInStage ? 0 : kOwnBytes);
+  static constexpr bool kFits = kBytes <= kShare;
+};
 
 // Waves per SIMD and the visited table from the distance policy
 // (M::waves_per_simd, M::ht_log2): one wave's gathers overlap the others'
@@ -120,23 +213,28 @@ __device__ __forceinline__ void eval_lines2(const M &m, const ResidentParams &p,
 // more queries and the batch ends when the last queries end, wherever they
 // run.
 template <int KPL, class M, class HT, bool N2S>
-__global__ __launch_bounds__(kWave, M::waves_per_simd(KPL)) void search_resident(ResidentParams p) {
+__global__ __launch_bounds__(kWave, M::waves_per_simd(KPL, HT::kWords)) void search_resident(ResidentParams p) {
   constexpr int kIdsPerLane = kCandCap / kWave;
+  using Lds = ResidentLds<KPL, M, HT, N2S>;
+  static_assert(Lds::kFits, "the waves this kernel is compiled for fit a CU's LDS");
 
   __shared__ __align__(16) uint32_t ht[HT::kWords];
-  __shared__ __align__(16) uint32_t cand[kCandCap];
+  __shared__ __align__(16) uint32_t own_cand[Lds::kInStage ? 1 : kCandCap];
   __shared__ uint32_t beam[KPL * kWave];  // W <= L
-  // candidates' byte offsets, worked out as they are compacted: the placement
-  // is then looked up beside the filter, for all ids of a group at once
-  constexpr bool kOffsets = M::kOffsets || (N2S && !M::kLocators && (M::kStream || M::kGathered));
+  // candidates' byte offsets (or slots), worked out as they are compacted: the
+  // placement is then looked up beside the filter, for all ids of a group at once
+  constexpr bool kOffsets = Lds::kOffsets, kSlots = Lds::kSlots;
   __shared__ __align__(16) uint64_t coff[kOffsets ? kCandCap : 1];
   __shared__ __align__(16) uint32_t qbuf[M::kQueryWords];
-  __shared__ __align__(16) uint32_t stage[M::stage_words(KPL) ? M::stage_words(KPL) : 1];
+  __shared__ __align__(16) uint32_t stage[Lds::kStageWords ? Lds::kStageWords : 1];
+  uint32_t *const cand = Lds::kInStage ? stage : own_cand;
+  [[maybe_unused]] uint32_t *const cand_slot = stage + kCandCap;
 
   const int l = lane_id();
   const uint32_t beams_per_group = min(kCandCap / p.R, (uint32_t)kWave);
   const uint32_t entry_word = M::cand_word(p.geom, p.entry);
-  const uint64_t entry_off = vec_offset(p.geom, slot_ct<N2S>(p.geom, p.entry));
+  const uint32_t entry_slot = slot_ct<N2S>(p.geom, p.entry);
+  const uint64_t entry_off = vec_offset(p.geom, entry_slot);
 
   unsigned long long n_eval = 0, n_reeval = 0, n_exp = 0, n_iter = 0;
 
@@ -256,7 +354,7 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL)) void search_resident
           }
         }
         [[maybe_unused]] uint32_t slot[kIdsPerLane];
-        if constexpr (kOffsets) {
+        if constexpr (kOffsets || kSlots) {
 #pragma unroll
           for (int t = 0; t < kIdsPerLane; ++t) slot[t] = slot_ct<N2S>(p.geom, valid[t] ? ids[t] : p.entry);
         }
@@ -272,6 +370,7 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL)) void search_resident
             const uint32_t at = M::cand_pos(cnt + lanes_below(mnew));
             cand[at] = M::cand_word(p.geom, ids[t]);
             if constexpr (kOffsets) coff[at] = vec_offset(p.geom, slot[t]);
+            if constexpr (kSlots) cand_slot[at] = slot[t];
           }
           cnt += (uint32_t)__popcll(mnew);
           ht_used += (uint32_t)__popcll(mrec);
@@ -297,20 +396,14 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL)) void search_resident
             default: break;
           }
         } else if constexpr (M::kGathered) {
-          auto off_of = [&](uint32_t i) {
-            if constexpr (kOffsets) return i < cnt ? coff[i] : entry_off;
-            else return vec_offset(p.geom, i < cnt ? cand[i] : p.entry);
-          };
-          if constexpr (M::two_batches(KPL)) {
-            switch ((cnt + kWave - 1) / kWave) {
-              case 1: eval_lines2<1, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
-              case 2: eval_lines2<2, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
-              case 3: eval_lines2<3, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
-              case 4: eval_lines2<4, KPL>(m, p, cand, off_of, cnt, F, forgot); break;
-              default: break;
-            }
-          } else if (cnt != 0) {
-            eval_lines<KPL>(m, p, cand, off_of, cnt, F, forgot);
+          if constexpr (Lds::kInStage) {
+            LaneCandidates<N2S> c;
+            c.read(cand, cand_slot, cnt, p.entry, entry_slot);
+            asm volatile("" ::: "memory");  // read before the stage is written (LDS operations of one wave are in order)
+            eval_group<KPL, M, HT::kWords>(m, p, c, cnt, F, forgot);
+          } else {
+            LdsCandidates<N2S> c{cand, coff, cnt, p.entry, entry_off};
+            eval_group<KPL, M, HT::kWords>(m, p, c, cnt, F, forgot);
           }
         } else {
           // batches of kBatch vectors, one round trip each

@@ -1,0 +1,49 @@
+"""Waves and LDS of the resident search kernels, checked by the compiler on the
+CPU: the kernels' own constants, asserted in a source that is only parsed.
+
+launch_bounds does not see LDS: a kernel whose tables, candidates and stage
+leave no room for the waves it is compiled for runs with fewer, silently."""
+import subprocess
+from pathlib import Path
+
+CSRC = Path(__file__).resolve().parents[1] / "paper_2607_04415_amd" / "csrc"
+
+HEAD = """
+#include "launch.hpp"
+using namespace gorio;
+template <int KPL, class M, bool N2S>
+constexpr bool fits() {
+  return ResidentLds<KPL, M, VisitedLds16<M::ht_log2(KPL)>, N2S>::kFits &&
+         ResidentLds<KPL, M, ResidentHtLarge, N2S>::kFits;
+}
+template <class M>
+constexpr bool all_fit() {
+  return fits<1, M, false>() && fits<2, M, false>() && fits<4, M, false>() && fits<1, M, true>() &&
+         fits<2, M, true>() && fits<4, M, true>();
+}
+// waves per SIMD that run with the 16-bit table
+template <int KPL, class M>
+constexpr int waves() {
+  return M::grid_waves_per_simd(KPL, VisitedLds16<M::ht_log2(KPL)>::kWords);
+}
+"""
+
+
+def holds(tmp_path, *conditions):
+    """Every condition is a constant expression the compiler finds true."""
+    from paper_2607_04415_amd import _build
+    src = tmp_path / "shape.hip"
+    src.write_text(HEAD + "".join(f"static_assert({c});\n" for c in conditions))
+    r = subprocess.run([_build.HIPCC, *_build.FLAGS, "--cuda-host-only", "-fsyntax-only", "-w", f"-I{CSRC}",
+                        f"-I{_build.INCLUDE}", str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, "\n".join(line for line in r.stderr.splitlines() if "error" in line)
+
+
+def test_the_waves_of_every_kernel_fit_a_cu(tmp_path):
+    lines = [f"all_fit<MetricF32Lines<{J}>>()" for J in range(1, 9)]
+    rows = ["all_fit<MetricU8Rows<1, true>>()", "all_fit<MetricU8Rows<1, false>>()", "all_fit<MetricU8Rows<2, false>>()"]
+    batches = ["all_fit<MetricU8<1, false>>()", "all_fit<MetricU8<16, false>>()", "all_fit<MetricU8<4, true, true>>()"]
+    # two waves for rows of up to four lines and frontiers of up to 64, one with the 32-bit table
+    two = [f"waves<1, MetricF32Lines<{J}>>() == 2" for J in (1, 2, 3, 4)]
+    one = [f"MetricF32Lines<{J}>::waves_per_simd({k}, ResidentHtLarge::kWords) == 1" for J in (1, 4, 8) for k in (1, 2, 4)]
+    holds(tmp_path, "all_fit<MetricF32Lines<3, true>>()", *lines, *rows, *batches, *two, *one)
