@@ -40,13 +40,13 @@ using ResidentHtLarge = VisitedLds<13>;
 
 namespace detail {
 
-// One workgroup per wave slot the device holds at once, but at most
-// `grid_waves_per_simd` per SIMD (queries beyond the grid are taken from the
-// kernel's counter), and at most `grid`.
+// Workgroups of a resident kernel's grid: one per wave slot the device holds
+// at once, but at most `grid_waves_per_simd` per SIMD (queries beyond the grid
+// are taken from the kernel's counter).
 template <auto Kernel, int grid_waves_per_simd>
-hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s) {
-  static int slots = 0;  // per kernel
-  if (slots == 0) {
+hipError_t resident_slots(int &slots) {
+  static int held = 0;  // per kernel
+  if (held == 0) {
     constexpr int kSimdsPerCu = 4;
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -54,8 +54,21 @@ hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s
     if (e == hipSuccess)
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(Kernel), kWave, 0);
     if (e != hipSuccess) return e;
-    slots = std::max(1, cus * std::min(per_cu, kSimdsPerCu * grid_waves_per_simd));
+    held = std::max(1, cus * std::min(per_cu, kSimdsPerCu * grid_waves_per_simd));
   }
+  slots = held;
+  return hipSuccess;
+}
+
+// `most`: do nothing (done = false) with more queries than the grid's workgroups.
+template <int KPL, class M, class HT, bool N2S>
+hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s, bool most, bool &done) {
+  constexpr auto Kernel = search_resident<KPL, M, HT, N2S>;
+  int slots = 0;
+  const hipError_t e = resident_slots<Kernel, M::grid_waves_per_simd(KPL, HT::kWords)>(slots);
+  if (e != hipSuccess) return e;
+  done = !most || p.nq <= (uint32_t)slots;
+  if (!done) return hipSuccess;
   Kernel<<<std::min(grid, slots), kWave, 0, s>>>(p);
   return hipGetLastError();
 }
@@ -63,13 +76,16 @@ hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s
 template <int KPL, class M, bool N2S>
 hipError_t resident_t(const ResidentParams &p, int grid, hipStream_t s) {
   using Small = VisitedLds16<M::ht_log2(KPL)>;
-  using Large = ResidentHtLarge;
-  if (M::kSmallIds || p.n <= Small::kMaxId)
-    return launch_resident_grid<search_resident<KPL, M, Small, N2S>, M::grid_waves_per_simd(KPL, Small::kWords)>(
-        p, grid, s);
-  if constexpr (!M::kSmallIds)
-    return launch_resident_grid<search_resident<KPL, M, Large, N2S>, M::grid_waves_per_simd(KPL, Large::kWords)>(
-        p, grid, s);
+  using Few = VisitedLds16<M::few_ht_log2(KPL)>;
+  bool done = false;
+  if constexpr (Few::kWords != Small::kWords) {
+    if (p.n <= Few::kMaxId) {
+      const hipError_t e = launch_resident_grid<KPL, M, Few, N2S>(p, grid, s, true, done);
+      if (done || e != hipSuccess) return e;
+    }
+  }
+  if (M::kSmallIds || p.n <= Small::kMaxId) return launch_resident_grid<KPL, M, Small, N2S>(p, grid, s, false, done);
+  if constexpr (!M::kSmallIds) return launch_resident_grid<KPL, M, ResidentHtLarge, N2S>(p, grid, s, false, done);
   return hipErrorInvalidValue;  // not reached: the caller checks p.n
 }
 

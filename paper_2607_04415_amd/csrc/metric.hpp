@@ -55,6 +55,7 @@ struct MetricU8 {
     return table_words > 4096 ? 1 : 2;
   }
   __host__ __device__ static constexpr int ht_log2(int kpl) { return VDW <= 4 && kpl == 1 ? 12 : 13; }
+  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return ht_log2(kpl); }
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;  // INT32_MAX
   static_assert(!LOC16 || (EXACT && VDW % 4 == 0), "locators address whole 16-byte units");
   static constexpr bool kLocators = LOC16;
@@ -290,6 +291,7 @@ struct MetricU8Rows {
     return table_words > 4096 ? 1 : 2;
   }
   __host__ __device__ static constexpr int ht_log2(int) { return 13; }
+  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return ht_log2(kpl); }
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;
   static constexpr bool kLocators = false, kGathered = false, kStream = true, kOffsets = true;
   static constexpr bool kSmallIds = false;
@@ -477,8 +479,16 @@ struct MetricF32Lines {
   static constexpr uint32_t kPadDist = 0x7F800000u;  // +inf
   // A line takes 32 registers: up to four lines, two waves per SIMD.  Long
   // frontiers meet more nodes than a 16 KB visited table records, and 32 KB
-  // (the 32-bit table too) leave room for one.
-  __host__ __device__ static constexpr int ht_log2(int kpl) { return J <= 4 && kpl == 1 ? 13 : 14; }
+  // (the 32-bit table too) leave room for one.  Rows of one or two lines are
+  // bound by filter, LDS and merge more than by the gather, and a second wave
+  // covers these: it is worth more than the records, also where half of the
+  // evaluations are repeats.  100k nodes, 5,000 queries, L=200, us a call with
+  // 32 KB and one wave / 16 KB and two: 20 floats, R=16 1,293 / 778, R=64 W=8
+  // 2,045 / 1,459 (repeats 1% / 21%); 64 floats 1,498 / 950, 2,634 / 1,911.
+  // A batch that leaves one wave per SIMD anyway has the larger table
+  // (few_ht_log2; 1,024 queries, 32 floats, R=64 W=8, L=200: 0.87 of the time).
+  __host__ __device__ static constexpr int ht_log2(int kpl) { return J <= 2 || (J <= 4 && kpl == 1) ? 13 : 14; }
+  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return kpl > 1 ? 14 : ht_log2(kpl); }
   __host__ __device__ static constexpr int waves_per_simd(int, uint32_t table_words) {
     return J <= 4 && table_words <= 4096 ? 2 : 1;
   }

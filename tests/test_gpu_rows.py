@@ -75,4 +75,5 @@ def test_beams(dtype, D, R, k, L, W):
                                      ("f32", 20), ("f32", 32), ("f32", 64), ("f32", 90), ("f32", 96), ("f32", 128),
                                      ("f32", 150), ("f32", 256)])
 def test_long_frontiers(dtype, D, L, layout, placed):
-    check(dtype, D, 64, 50, L, 8, layout, placed, counts=(None,))
+    # 1,000: past the teams of eight, at most one wave per SIMD
+    check(dtype, D, 64, 50, L, 8, layout, placed, counts=(1000, None))

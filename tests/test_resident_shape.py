@@ -14,6 +14,7 @@ using namespace gorio;
 template <int KPL, class M, bool N2S>
 constexpr bool fits() {
   return ResidentLds<KPL, M, VisitedLds16<M::ht_log2(KPL)>, N2S>::kFits &&
+         ResidentLds<KPL, M, VisitedLds16<M::few_ht_log2(KPL)>, N2S>::kFits &&
          ResidentLds<KPL, M, ResidentHtLarge, N2S>::kFits;
 }
 template <class M>
@@ -47,3 +48,10 @@ def test_the_waves_of_every_kernel_fit_a_cu(tmp_path):
     two = [f"waves<1, MetricF32Lines<{J}>>() == 2" for J in (1, 2, 3, 4)]
     one = [f"MetricF32Lines<{J}>::waves_per_simd({k}, ResidentHtLarge::kWords) == 1" for J in (1, 4, 8) for k in (1, 2, 4)]
     holds(tmp_path, "all_fit<MetricF32Lines<3, true>>()", *lines, *rows, *batches, *two, *one)
+
+
+def test_short_float32_rows_keep_two_waves_at_any_frontier(tmp_path):
+    # rows of one or two lines: 16 KB table, two waves; a batch of one wave per SIMD has 32 KB
+    holds(tmp_path, *[f"waves<{k}, MetricF32Lines<{J}>>() == 2" for J in (1, 2) for k in (1, 2, 4)],
+          *[f"MetricF32Lines<{J}>::few_ht_log2({k}) == 14" for J in (1, 2) for k in (2, 4)],
+          *[f"waves<{k}, MetricF32Lines<{J}>>() == 1" for J in (3, 4, 8) for k in (2, 4)])
