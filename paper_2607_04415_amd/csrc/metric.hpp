@@ -483,10 +483,10 @@ struct MetricF32Lines {
   // bound by filter, LDS and merge more than by the gather, and a second wave
   // covers these: it is worth more than the records, also where half of the
   // evaluations are repeats.  100k nodes, 5,000 queries, L=200, us a call with
-  // 32 KB and one wave / 16 KB and two: 20 floats, R=16 1,293 / 778, R=64 W=8
-  // 2,045 / 1,459 (repeats 1% / 21%); 64 floats 1,498 / 950, 2,634 / 1,911.
+  // 32 KB and one wave / 16 KB and two: 20 floats, R=16 1,292 / 867, R=64 W=8
+  // 2,036 / 1,393 (repeats 1% / 21%); 64 floats 1,497 / 957, 2,647 / 1,977.
   // A batch that leaves one wave per SIMD anyway has the larger table
-  // (few_ht_log2; 1,024 queries, 32 floats, R=64 W=8, L=200: 0.87 of the time).
+  // (few_ht_log2; 200k x 32, R=64, W=8, L=200, 1,024 queries 548 / 632).
   __host__ __device__ static constexpr int ht_log2(int kpl) { return J <= 2 || (J <= 4 && kpl == 1) ? 13 : 14; }
   __host__ __device__ static constexpr int few_ht_log2(int kpl) { return kpl > 1 ? 14 : ht_log2(kpl); }
   __host__ __device__ static constexpr int waves_per_simd(int, uint32_t table_words) {
