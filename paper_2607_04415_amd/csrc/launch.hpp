@@ -84,9 +84,8 @@ hipError_t resident_t(const ResidentParams &p, int grid, hipStream_t s) {
       if (done || e != hipSuccess) return e;
     }
   }
-  if (M::kSmallIds || p.n <= Small::kMaxId) return launch_resident_grid<KPL, M, Small, N2S>(p, grid, s, false, done);
-  if constexpr (!M::kSmallIds) return launch_resident_grid<KPL, M, ResidentHtLarge, N2S>(p, grid, s, false, done);
-  return hipErrorInvalidValue;  // not reached: the caller checks p.n
+  if (p.n <= Small::kMaxId) return launch_resident_grid<KPL, M, Small, N2S>(p, grid, s, false, done);
+  return launch_resident_grid<KPL, M, ResidentHtLarge, N2S>(p, grid, s, false, done);
 }
 
 // Small batches: a team of waves per query while the chip holds all of them at

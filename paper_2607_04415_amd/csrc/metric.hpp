@@ -59,7 +59,6 @@ struct MetricU8 {
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;  // INT32_MAX
   static_assert(!LOC16 || (EXACT && VDW % 4 == 0), "locators address whole 16-byte units");
   static constexpr bool kLocators = LOC16;
-  static constexpr bool kSmallIds = false;
   static constexpr bool kStream = LOC16;    // chunks of 64, two in flight
   static constexpr bool kOffsets = false;   // candidates' byte offsets kept in LDS
   __host__ __device__ static constexpr uint32_t stage_words(int, uint32_t) { return 0; }  // LDS of a wave for set_stage
@@ -294,7 +293,6 @@ struct MetricU8Rows {
   __host__ __device__ static constexpr int few_ht_log2(int kpl) { return ht_log2(kpl); }
   static constexpr uint32_t kPadDist = 0x7FFFFFFFu;
   static constexpr bool kLocators = false, kGathered = false, kStream = true, kOffsets = true;
-  static constexpr bool kSmallIds = false;
   __host__ __device__ static constexpr uint32_t stage_words(int, uint32_t) { return 0; }
   __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 ? 8 : 4; }
   __host__ __device__ static constexpr int team_per_simd() { return 2; }
@@ -472,7 +470,7 @@ struct MetricF32 {  // paged kernels: one lane per candidate, records in the pag
 // the same line of the next batch is read into them.  Bound by random line
 // reads: 300k x 128, R=32, L=64, 5,000 queries 2.79 ms with a lane per vector
 // (1.8 TB/s), 0.81 ms now (6.5 TB/s; such reads reach 6.8); 256-d 3.78 -> 1.27.
-// EXACT: every line is whole (D = 32 J); for the 16-bit visited tables only.
+// EXACT: every line is whole (D = 32 J).
 template <int J, bool EXACT = false>
 struct MetricF32Lines {
   static constexpr int kQueryWords = 32 * J;
@@ -498,14 +496,17 @@ struct MetricF32Lines {
   // compiler may overlap one line's sums with the next lines' passes and keep
   // the query in registers; for whole lines two batches are in flight (1M x
   // 96, L=128, W=8, 10k queries: 5.27 ms without any of it, 4.83 with the
-  // ragged line's tests, 4.18 now).  Not with four frontier registers: there
-  // they take the registers the overlap needs (100k x 96, L=200, 5,000 queries:
-  // R=16 1,541 us with one batch and 1,672 with two, R=64 2,650 and 2,883).
+  // ragged line's tests, 4.18 now; with the 32-bit table, 2^24 + 4,099 nodes,
+  // R=16, 5,000 queries: L=64 906 us ragged and 838 whole, L=128 1,370 and
+  // 1,288).  Not with four frontier registers: there they take the registers
+  // the overlap needs (100k x 96, L=200, 5,000 queries: R=16 1,541 us with one
+  // batch and 1,672 with two, R=64 2,650 and 2,883).
   __host__ __device__ static constexpr bool roomy(int kpl, uint32_t w) { return waves_per_simd(kpl, w) == 1 && J <= 4; }
-  __host__ __device__ static constexpr bool two_batches(int kpl, uint32_t w) { return EXACT && roomy(kpl, w) && kpl == 2; }
+  __host__ __device__ static constexpr bool two_batches(int kpl, uint32_t w) {
+    return EXACT && J <= 3 && roomy(kpl, w) && kpl <= 2;
+  }
   __host__ __device__ static constexpr uint32_t stage_words(int kpl, uint32_t w) { return roomy(kpl, w) ? 1024 : 512; }
   static constexpr bool kLocators = false, kStream = false, kOffsets = false, kGathered = true;
-  static constexpr bool kSmallIds = EXACT;  // only indexes whose ids fit the 16-bit tables
 
   __device__ __forceinline__ static void pad_round(uint32_t *, uint64_t *, uint32_t, uint32_t, uint64_t) {}
   __device__ __forceinline__ static uint32_t cand_pos(uint32_t i) { return i; }

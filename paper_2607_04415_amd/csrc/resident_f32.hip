@@ -17,7 +17,7 @@ hipError_t launch_resident_f32(const ResidentParams &p, int grid, hipStream_t s)
     case 3:
       // whole lines: the ragged line's tests cost a kernel with one wave per
       // SIMD its overlap (1M x 96, L=128, W=8, 10k queries: 4.83 against 4.18 ms)
-      if (p.D == 96 && p.n <= VisitedLds16<13>::kMaxId) return launch_resident_f32_whole3(p, grid, s);
+      if (p.D == 96) return launch_resident_f32_whole3(p, grid, s);
       return launch_resident_f32_lines<3>(p, grid, s);
     case 4: return launch_resident_f32_lines<4>(p, grid, s);
     case 5: return launch_resident_f32_lines<5>(p, grid, s);

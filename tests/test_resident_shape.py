@@ -55,3 +55,10 @@ def test_short_float32_rows_keep_two_waves_at_any_frontier(tmp_path):
     holds(tmp_path, *[f"waves<{k}, MetricF32Lines<{J}>>() == 2" for J in (1, 2) for k in (1, 2, 4)],
           *[f"MetricF32Lines<{J}>::few_ht_log2({k}) == 14" for J in (1, 2) for k in (2, 4)],
           *[f"waves<{k}, MetricF32Lines<{J}>>() == 1" for J in (3, 4, 8) for k in (2, 4)])
+
+
+def test_whole_lines_have_two_batches_in_flight_with_either_table(tmp_path):
+    large = "ResidentHtLarge::kWords"
+    holds(tmp_path, "all_fit<MetricF32Lines<3, true>>()",
+          *[f"MetricF32Lines<3, true>::two_batches({k}, {large})" for k in (1, 2)],
+          "MetricF32Lines<3, true>::two_batches(2, VisitedLds16<14>::kWords)")
