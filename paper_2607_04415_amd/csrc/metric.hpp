@@ -500,7 +500,8 @@ struct MetricF32Lines {
   // R=16, 5,000 queries: L=64 906 us ragged and 838 whole, L=128 1,370 and
   // 1,288).  Not with four frontier registers: there they take the registers
   // the overlap needs (100k x 96, L=200, 5,000 queries: R=16 1,541 us with one
-  // batch and 1,672 with two, R=64 2,650 and 2,883).
+  // batch and 1,672 with two, R=64 2,650 and 2,883), nor with four lines,
+  // whose second batch spills (100k x 128, R=16, L=100: 925 and 2,286).
   __host__ __device__ static constexpr bool roomy(int kpl, uint32_t w) { return waves_per_simd(kpl, w) == 1 && J <= 4; }
   __host__ __device__ static constexpr bool two_batches(int kpl, uint32_t w) {
     return EXACT && J <= 3 && roomy(kpl, w) && kpl <= 2;

@@ -8,6 +8,7 @@ hipError_t launch_resident_f32_lines(const ResidentParams &p, int grid, hipStrea
 
 template <>
 hipError_t launch_resident_f32_lines<1>(const ResidentParams &p, int grid, hipStream_t s) {
+  if (p.D == 32) return detail::resident<MetricF32Lines<1, true>>(p, grid, s);
   return detail::resident<MetricF32Lines<1>>(p, grid, s);
 }
 

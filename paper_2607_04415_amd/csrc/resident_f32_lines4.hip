@@ -8,6 +8,7 @@ hipError_t launch_resident_f32_lines(const ResidentParams &p, int grid, hipStrea
 
 template <>
 hipError_t launch_resident_f32_lines<4>(const ResidentParams &p, int grid, hipStream_t s) {
+  if (p.D == 128) return detail::resident<MetricF32Lines<4, true>>(p, grid, s);
   return detail::resident<MetricF32Lines<4>>(p, grid, s);
 }
 

@@ -8,6 +8,7 @@ hipError_t launch_resident_f32_lines(const ResidentParams &p, int grid, hipStrea
 
 template <>
 hipError_t launch_resident_f32_lines<6>(const ResidentParams &p, int grid, hipStream_t s) {
+  if (p.D == 192) return detail::resident<MetricF32Lines<6, true>>(p, grid, s);
   return detail::resident<MetricF32Lines<6>>(p, grid, s);
 }
 

@@ -8,6 +8,7 @@ hipError_t launch_resident_f32_lines(const ResidentParams &p, int grid, hipStrea
 
 template <>
 hipError_t launch_resident_f32_lines<7>(const ResidentParams &p, int grid, hipStream_t s) {
+  if (p.D == 224) return detail::resident<MetricF32Lines<7, true>>(p, grid, s);
   return detail::resident<MetricF32Lines<7>>(p, grid, s);
 }
 

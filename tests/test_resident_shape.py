@@ -41,13 +41,13 @@ def holds(tmp_path, *conditions):
 
 
 def test_the_waves_of_every_kernel_fit_a_cu(tmp_path):
-    lines = [f"all_fit<MetricF32Lines<{J}>>()" for J in range(1, 9)]
+    lines = [f"all_fit<MetricF32Lines<{J}, {whole}>>()" for J in range(1, 9) for whole in ("false", "true")]
     rows = ["all_fit<MetricU8Rows<1, true>>()", "all_fit<MetricU8Rows<1, false>>()", "all_fit<MetricU8Rows<2, false>>()"]
     batches = ["all_fit<MetricU8<1, false>>()", "all_fit<MetricU8<16, false>>()", "all_fit<MetricU8<4, true, true>>()"]
     # two waves for rows of up to four lines and frontiers of up to 64, one with the 32-bit table
     two = [f"waves<1, MetricF32Lines<{J}>>() == 2" for J in (1, 2, 3, 4)]
     one = [f"MetricF32Lines<{J}>::waves_per_simd({k}, ResidentHtLarge::kWords) == 1" for J in (1, 4, 8) for k in (1, 2, 4)]
-    holds(tmp_path, "all_fit<MetricF32Lines<3, true>>()", *lines, *rows, *batches, *two, *one)
+    holds(tmp_path, *lines, *rows, *batches, *two, *one)
 
 
 def test_short_float32_rows_keep_two_waves_at_any_frontier(tmp_path):
@@ -59,6 +59,5 @@ def test_short_float32_rows_keep_two_waves_at_any_frontier(tmp_path):
 
 def test_whole_lines_have_two_batches_in_flight_with_either_table(tmp_path):
     large = "ResidentHtLarge::kWords"
-    holds(tmp_path, "all_fit<MetricF32Lines<3, true>>()",
-          *[f"MetricF32Lines<3, true>::two_batches({k}, {large})" for k in (1, 2)],
+    holds(tmp_path, *[f"MetricF32Lines<3, true>::two_batches({k}, {large})" for k in (1, 2)],
           "MetricF32Lines<3, true>::two_batches(2, VisitedLds16<14>::kWords)")
