@@ -10,9 +10,10 @@
 //               v_dot4_u32_u8 on coalesced reads, 8 lanes per vector.
 //   MetricU8Rows - the same for rows of other lengths, arrangements and
 //               placements (resident).
-//   MetricF32, MetricF32Lines - one lane per candidate (the resident kernel
-//               gathers 8 lanes per vector by whole lines and hands the
-//               blocks to their lanes through LDS);
+//   MetricF32, MetricF32Lines, MetricF32Own - one lane per candidate (the
+//               resident kernel gathers 8 lanes per vector by whole lines and
+//               hands the blocks to their lanes through LDS; rows of up to 8
+//               floats are read by their own lane);
 //               t = q_d - x_d, acc = acc + t*t for d = 0 .. D-1 in order,
 //               every operation rounded to nearest even with no fused
 //               multiply-add, so the result is the same float as a plain
@@ -658,6 +659,83 @@ struct MetricF32Lines {
     return __float_as_uint(acc);
   }
   // Distance bits of one record (`off` the same in every lane).
+  __device__ __forceinline__ uint32_t dist_one(const uint8_t *pages, uint64_t off) const {
+    Batch b;
+    issue(pages, off, b);
+    return dist<false>(b);
+  }
+};
+
+// Resident kernel: rows of at most 8 floats, at most two 16-byte blocks, which
+// the lane that sums them reads itself.  A line gather would read such rows
+// with eight lanes each and pass them through LDS: one load instruction per 8
+// vectors and 10 LDS accesses per 16, where a lane's own block is one or two
+// loads for all 64.  100k nodes, 5,000 queries, us a call with a lane per vector
+// and dword loads / the line gather / here: 4 floats, R=64, W=8, L=64 420 / 435
+// / 305; 8 floats 457 / 434 / 330; 4 floats, placed, R=32, L=200 941 / 1,834 /
+// 744.  Rows of 9 to 16 floats (three or four blocks) are as fast either way.
+struct MetricF32Own {
+  static constexpr int kQueryWords = 8;
+  static constexpr uint32_t kPadDist = 0x7F800000u;  // +inf
+  // two waves and 16 KB, as MetricF32Lines of one line
+  __host__ __device__ static constexpr int ht_log2(int) { return 13; }
+  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return ht_log2(kpl); }
+  __host__ __device__ static constexpr int waves_per_simd(int, uint32_t table_words) { return table_words > 4096 ? 1 : 2; }
+  __host__ __device__ static constexpr int grid_waves_per_simd(int kpl, uint32_t w) { return waves_per_simd(kpl, w); }
+  __host__ __device__ static constexpr bool roomy(int, uint32_t) { return false; }
+  __host__ __device__ static constexpr bool two_batches(int, uint32_t) { return false; }
+  __host__ __device__ static constexpr uint32_t stage_words(int, uint32_t) { return 512; }  // ids and slots only
+  static constexpr bool kLocators = false, kStream = false, kOffsets = false, kGathered = true;
+  __device__ __forceinline__ static void pad_round(uint32_t *, uint64_t *, uint32_t, uint32_t, uint64_t) {}
+  __device__ __forceinline__ static uint32_t cand_pos(uint32_t i) { return i; }
+  __device__ __forceinline__ static uint32_t cand_word(const PageGeom &, uint32_t v) { return v; }
+
+  __host__ __device__ static constexpr int team_waves(int kpl) { return kpl > 1 ? 8 : 4; }
+  __host__ __device__ static constexpr int team_per_simd() { return 2; }
+  __host__ __device__ static constexpr int team_ht_log2(int kpl) { return kpl > 1 ? 14 : 13; }
+  static constexpr int kTeamStageWords = 0;
+  __device__ __forceinline__ void set_stage(uint32_t *) {}
+
+  float q[8];  // zeros past D
+  uint32_t D;
+
+  __device__ __forceinline__ void load_query(const void *queries, uint32_t qi, uint32_t D_, uint32_t *) {
+    D = D_;
+    const float *src = static_cast<const float *>(queries) + (uint64_t)qi * D_;
+#pragma unroll
+    for (uint32_t d = 0; d < 8; ++d) q[d] = d < D_ ? src[d] : 0.0f;
+  }
+
+  struct Batch {
+    uint4 x[2];
+  };
+  // The last block may reach up to 12 bytes past the vector: the page array
+  // ends with 16 spare bytes).
+  __device__ __forceinline__ void issue(const uint8_t *pages, uint64_t off, Batch &b) const {
+    const uint32_t *w = reinterpret_cast<const uint32_t *>(pages + off);
+    __builtin_memcpy(&b.x[0], __builtin_assume_aligned(w, 4), 16);
+    b.x[1] = make_uint4(0u, 0u, 0u, 0u);
+    if (D > 4) __builtin_memcpy(&b.x[1], __builtin_assume_aligned(w + 4, 4), 16);
+  }
+  // Both the query and, past D, the vector are made 0: adding (0 - 0)^2 leaves
+  // the sum as it is.
+  template <bool ROOMY>
+  __device__ __forceinline__ uint32_t dist(const Batch &b) const {
+    const uint32_t x[8] = {b.x[0].x, b.x[0].y, b.x[0].z, b.x[0].w, b.x[1].x, b.x[1].y, b.x[1].z, b.x[1].w};
+    float acc = 0.0f;
+#pragma unroll
+    for (uint32_t d = 0; d < 8; ++d) {
+      const float t = __fsub_rn(q[d], __uint_as_float(d < D ? x[d] : 0u));
+      acc = __fadd_rn(acc, __fmul_rn(t, t));
+    }
+    return __float_as_uint(acc);
+  }
+  template <bool ROOMY>
+  __device__ __forceinline__ uint32_t dist_and_issue(const uint8_t *pages, uint64_t next, Batch &b) const {
+    const Batch now = b;
+    issue(pages, next, b);
+    return dist<ROOMY>(now);
+  }
   __device__ __forceinline__ uint32_t dist_one(const uint8_t *pages, uint64_t off) const {
     Batch b;
     issue(pages, off, b);

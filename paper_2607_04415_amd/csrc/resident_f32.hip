@@ -14,7 +14,10 @@ namespace gorio {
 template <int J>
 hipError_t launch_resident_f32_lines(const ResidentParams &p, int grid, hipStream_t s);
 
+hipError_t launch_resident_f32_own(const ResidentParams &p, int grid, hipStream_t s);  // resident_f32_own.hip
+
 hipError_t launch_resident_f32(const ResidentParams &p, int grid, hipStream_t s) {
+  if (p.D <= 8) return launch_resident_f32_own(p, grid, s);
   switch ((p.D + 31) / 32) {
     case 1: return launch_resident_f32_lines<1>(p, grid, s);
     case 2: return launch_resident_f32_lines<2>(p, grid, s);

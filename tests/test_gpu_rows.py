@@ -53,7 +53,7 @@ def test_u8_rows(D, layout, placed):
 
 
 @pytest.mark.parametrize("layout,placed", [("vectors", False), ("contiguous", False), ("contiguous", True)])
-@pytest.mark.parametrize("D", [1, 3, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 192, 223, 256])
+@pytest.mark.parametrize("D", [1, 3, 4, 5, 8, 9, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 192, 223, 256])
 def test_f32_rows(D, layout, placed):
     check("f32", D, 20, 10, 40, 4, layout, placed)
 

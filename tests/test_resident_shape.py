@@ -47,7 +47,7 @@ def test_the_waves_of_every_kernel_fit_a_cu(tmp_path):
     # two waves for rows of up to four lines and frontiers of up to 64, one with the 32-bit table
     two = [f"waves<1, MetricF32Lines<{J}>>() == 2" for J in (1, 2, 3, 4)]
     one = [f"MetricF32Lines<{J}>::waves_per_simd({k}, ResidentHtLarge::kWords) == 1" for J in (1, 4, 8) for k in (1, 2, 4)]
-    holds(tmp_path, *lines, *rows, *batches, *two, *one)
+    holds(tmp_path, "all_fit<MetricF32Own>()", "waves<4, MetricF32Own>() == 2", *lines, *rows, *batches, *two, *one)
 
 
 def test_short_float32_rows_keep_two_waves_at_any_frontier(tmp_path):
