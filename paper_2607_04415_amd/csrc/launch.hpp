@@ -43,7 +43,7 @@ namespace detail {
 // Workgroups of a resident kernel's grid: one per wave slot the device holds
 // at once, but at most `grid_waves_per_simd` per SIMD (queries beyond the grid
 // are taken from the kernel's counter).
-template <auto Kernel, int grid_waves_per_simd>
+template <auto Kernel, int grid_waves_per_simd, uint32_t lds>
 hipError_t resident_slots(int &slots) {
   static int held = 0;  // per kernel
   if (held == 0) {
@@ -52,7 +52,7 @@ hipError_t resident_slots(int &slots) {
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(Kernel), kWave, 0);
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(Kernel), kWave, lds);
     if (e != hipSuccess) return e;
     held = std::max(1, cus * std::min(per_cu, kSimdsPerCu * grid_waves_per_simd));
   }
@@ -65,11 +65,12 @@ template <int KPL, class M, class HT, bool N2S>
 hipError_t launch_resident_grid(const ResidentParams &p, int grid, hipStream_t s, bool most, bool &done) {
   constexpr auto Kernel = search_resident<KPL, M, HT, N2S>;
   int slots = 0;
-  const hipError_t e = resident_slots<Kernel, M::grid_waves_per_simd(KPL, HT::kWords)>(slots);
+  constexpr uint32_t kLds = ResidentLds<KPL, M, HT, N2S>::kLaunchBytes;
+  const hipError_t e = resident_slots<Kernel, M::grid_waves_per_simd(KPL, HT::kWords), kLds>(slots);
   if (e != hipSuccess) return e;
   done = !most || p.nq <= (uint32_t)slots;
   if (!done) return hipSuccess;
-  Kernel<<<std::min(grid, slots), kWave, 0, s>>>(p);
+  Kernel<<<std::min(grid, slots), kWave, kLds, s>>>(p);
   return hipGetLastError();
 }
 

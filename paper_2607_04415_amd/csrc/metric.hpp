@@ -42,16 +42,22 @@ struct MetricU8 {
   static constexpr int kChunks = kBatch / kWave;
   static_assert(kRounds % 8 == 0, "rounds are reduced eight at a time");
   static constexpr int kQueryWords = 1;          // the query lives in registers
-  // resident kernel: waves per SIMD (registers, LDS), those of the grid, and
-  // the 16-bit visited table.  Frontiers of up to 64: 4096 entries in 8 KB and
+  // resident kernel: waves per SIMD that its registers leave room for, those of
+  // the grid, and the 16-bit visited table.  Frontiers of up to 64: 4096 entries in 8 KB and
   // 128 registers; the grid holds two waves per SIMD, which keep the gathers
   // saturated (a 100k-query batch on the 1M x 128-d index runs at the same
   // rate with two or four per SIMD) while each query, and so a batch's tail,
   // finishes sooner (10k queries: 0.79 ms against 0.85 ms with four).  Longer
   // frontiers meet more nodes than 4096 entries record (L=128, W=8, R=64: 80M
   // of 148M evaluations were repeats), and two waves per SIMD leave room for
-  // 16 KB each.
-  __host__ __device__ static constexpr int waves_per_simd(int kpl, uint32_t) { return VDW <= 4 && kpl == 1 ? 4 : 2; }
+  // 16 KB each.  Their kernels are still scheduled for four: the schedule for
+  // two is 2 to 4% slower (100k nodes, R=16, 5,000 queries, us a call: 128
+  // bytes, L=128 449 for two and 441 for four; 32 bytes, L=200 834 and 814;
+  // 16 bytes, L=200 755 and 732), but for locators with four frontier
+  // registers, which do not fit 128 (L=200 735 and 804).
+  __host__ __device__ static constexpr int waves_per_simd(int kpl, uint32_t) {
+    return VDW <= 4 && !(LOC16 && kpl > 2) ? 4 : 2;
+  }
   __host__ __device__ static constexpr int grid_waves_per_simd(int, uint32_t table_words) {
     return table_words > 4096 ? 1 : 2;
   }
@@ -710,7 +716,7 @@ struct MetricF32Own {
     uint4 x[2];
   };
   // The last block may reach up to 12 bytes past the vector: the page array
-  // ends with 16 spare bytes).
+  // ends with 16 spare bytes.
   __device__ __forceinline__ void issue(const uint8_t *pages, uint64_t off, Batch &b) const {
     const uint32_t *w = reinterpret_cast<const uint32_t *>(pages + off);
     __builtin_memcpy(&b.x[0], __builtin_assume_aligned(w, 4), 16);

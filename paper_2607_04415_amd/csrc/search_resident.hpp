@@ -203,6 +203,11 @@ struct ResidentLds {
   static constexpr bool kOffsets = kPlaced && !kInStage, kSlots = kPlaced && kInStage;
   static constexpr uint32_t kBytes = kOtherBytes + (kInStage ? 0 : kOwnBytes);
   static constexpr bool kFits = kBytes <= kShare;
+  // The compiler schedules for no more waves than the LDS it sees leaves room
+  // for; a kernel that is to be scheduled for more than run takes its table as
+  // the launch's LDS (16-bit tables).
+  static constexpr bool kHidden = kBytes > 160 * 1024 / 4 / kCompiled && HT::kWords <= 4096;
+  static constexpr uint32_t kLaunchBytes = kHidden ? 4 * HT::kWords : 0;
 };
 
 // Waves per SIMD and the visited table from the distance policy
@@ -218,7 +223,9 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL, HT::kWords)) void sea
   using Lds = ResidentLds<KPL, M, HT, N2S>;
   static_assert(Lds::kFits, "the waves this kernel is compiled for fit a CU's LDS");
 
-  __shared__ __align__(16) uint32_t ht[HT::kWords];
+  extern __shared__ __align__(16) uint32_t launch_lds[];
+  __shared__ __align__(16) uint32_t static_table[Lds::kLaunchBytes ? 1 : HT::kWords];
+  uint32_t *const ht = Lds::kLaunchBytes ? launch_lds : static_table;
   __shared__ __align__(16) uint32_t own_cand[Lds::kInStage ? 1 : kCandCap];
   __shared__ uint32_t beam[KPL * kWave];  // W <= L
   // candidates' byte offsets (or slots), worked out as they are compacted: the
@@ -411,7 +418,7 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL, HT::kWords)) void sea
             uint64_t key[M::kChunks];
             m.template resident_keys<N2S>(p.pages, p.geom, cand, c0, cnt, p.entry, key);
 #pragma unroll
-            for (int c = 0; c < M::kChunks; ++c) merge_keys<KPL>(F, key[c], forgot, p.L);
+            for (int c = 0; c < M::kChunks; ++c) merge_keys<KPL, KPL == 1>(F, key[c], forgot, p.L);
           }
         }
         __syncthreads();

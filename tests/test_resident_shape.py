@@ -61,3 +61,16 @@ def test_whole_lines_have_two_batches_in_flight_with_either_table(tmp_path):
     large = "ResidentHtLarge::kWords"
     holds(tmp_path, *[f"MetricF32Lines<3, true>::two_batches({k}, {large})" for k in (1, 2)],
           "MetricF32Lines<3, true>::two_batches(2, VisitedLds16<14>::kWords)")
+
+
+def test_uint8_kernels_of_long_frontiers_are_scheduled_for_four_waves(tmp_path):
+    # two run (16 KB table); the compiler must not see the table, or it schedules for two
+    small = "VisitedLds16<13>"
+    lds = [f"ResidentLds<{k}, {m}, {small}, {n}>" for m, k, n in (
+        ("MetricU8<4, true, true>", 2, "false"), ("MetricU8<1, false>", 2, "true"), ("MetricU8<1, false>", 4, "false"))]
+    holds(tmp_path, *[f"{x}::kCompiled == 4 && {x}::kGrid == 2 && {x}::kLaunchBytes == 16384" for x in lds],
+          # nothing to gain where as many waves run as the registers leave room for
+          f"ResidentLds<4, MetricU8<4, true, true>, {small}, false>::kLaunchBytes == 0",
+          "ResidentLds<1, MetricU8<4, true, true>, VisitedLds16<12>, false>::kLaunchBytes == 0",
+          *[f"ResidentLds<{k}, MetricU8Rows<1, true>, {small}, true>::kLaunchBytes == 0" for k in (1, 2, 4)],
+          *[f"ResidentLds<{k}, MetricF32Lines<1>, {small}, true>::kLaunchBytes == 0" for k in (1, 2, 4)])
