@@ -90,11 +90,27 @@ hipError_t resident_t(const ResidentParams &p, int grid, hipStream_t s) {
 }
 
 // Small batches: a team of waves per query while the chip holds all of them at
-// once; `done` tells whether the batch was launched.  Past that the teams'
-// idle waves cost more than the shorter chain saves (1M x 128 uint8, L=64:
-// 1,024 queries 140 us with teams, 197 with a wave each; 2,048 246 and 259;
-// L=128, where 512 teams fit: 512 queries 287 and 391 us, 1,024 415 and 394;
-// 300k x 128 float32, L=64, 512 fit: 178 and 272, 1,024 322 and 297).
+// once.  Past that a batch's last teams wait for slots that a wave each would
+// have filled.  With one frontier register the two are within 6% there for
+// uint8 (1M x 128, L=64, 2,048 queries, where 1,280 fit: 246 us with teams, 259
+// without), and teams have 0.85 of the speed for 96 floats (200k, L=32, beams of
+// 512 ids, 2,048 queries); with more registers they fall to half (200k x 128
+// uint8, L=128, beams of 512 ids, where 512 fit: 1,024 queries 0.83 of the
+// speed, 2,048 0.57).
+//
+// Waves of a team, from the ids of a beam (W R): enough for its 64s of
+// candidates, and 8 past 256 where frontiers are long.  A wave without
+// candidates still crosses four barriers an iteration and repeats every merge,
+// and its place could hold another team.  200k nodes, L=200, teams of 8
+// against the width here, speed at 1 / 512 / 1,024 queries: 128-byte uint8, up
+// to 64 ids 1.11 / 1.29 / 1.12, 128 ids 1.10 / 1.24 / 1.22, 256 ids 1.06 / 1.26 /
+// 1.05; 96 floats 1.06 / 1.01 / 1.01, 1.05 / 1.17 / 1.15, 1.02 / 1.32 / 1.00.
+// Two waves also where 64 ids would fit one: 1.04 to 1.23 times the speed of a
+// wave per query (one query).
+constexpr int team_width(uint32_t beam_ids, int most) {
+  return beam_ids <= 2 * kWave ? 2 : beam_ids <= 4 * kWave ? 4 : most;
+}
+
 template <int KPL, class M, int T>
 hipError_t team_t(const ResidentParams &p, hipStream_t s, bool &done) {
   constexpr auto Kernel = search_team<KPL, M, VisitedLds16<M::team_ht_log2(KPL)>, T>;
@@ -114,16 +130,21 @@ hipError_t team_t(const ResidentParams &p, hipStream_t s, bool &done) {
   return hipGetLastError();
 }
 
+template <int KPL, class M>
+hipError_t team_of_width(const ResidentParams &p, hipStream_t s, bool &done) {
+  const int width = team_width(p.W * p.R, M::team_waves(KPL));
+  if (width == 2) return team_t<KPL, M, 2>(p, s, done);
+  if constexpr (M::team_waves(KPL) > 4)
+    if (width > 4) return team_t<KPL, M, M::team_waves(KPL)>(p, s, done);
+  return team_t<KPL, M, 4>(p, s, done);
+}
+
 // frontier slots per lane (L <= 64 KPL)
 template <class M>
 hipError_t team(const ResidentParams &p, hipStream_t s, bool &done) {
-  if (p.L <= 64) {
-    // beams of up to 128 ids keep two waves busy
-    if (p.W * p.R <= 2 * kWave) return team_t<1, M, 2>(p, s, done);
-    return team_t<1, M, M::team_waves(1)>(p, s, done);
-  }
-  if (p.L <= 128) return team_t<2, M, M::team_waves(2)>(p, s, done);
-  return team_t<4, M, M::team_waves(4)>(p, s, done);
+  if (p.L <= 64) return team_of_width<1, M>(p, s, done);
+  if (p.L <= 128) return team_of_width<2, M>(p, s, done);
+  return team_of_width<4, M>(p, s, done);
 }
 
 // frontier slots per lane (L <= 64 KPL) and node_to_slot presence

@@ -62,7 +62,10 @@ def test_f32_rows(D, layout, placed):
 # of up to 256 ids, a beam wider than a team
 @pytest.mark.parametrize("dtype,D", [("u8", 128), ("u8", 100), ("f32", 96), ("f32", 160)])
 @pytest.mark.parametrize("R,k,L,W", [(64, 10, 64, 1), (64, 64, 64, 9), (65, 10, 65, 8), (1, 1, 128, 128), (96, 100, 128, 5),
-                                     (256, 10, 129, 3), (33, 200, 256, 256), (12, 12, 12, 12)])
+                                     (256, 10, 129, 3), (33, 200, 256, 256), (12, 12, 12, 12),
+                                     # each width of a team with each frontier: up to 128, 256 and more ids
+                                     (128, 10, 100, 1), (43, 10, 200, 3), (129, 10, 100, 1), (64, 10, 200, 4),
+                                     (16, 20, 200, 1), (86, 10, 64, 3), (43, 10, 64, 3)])
 def test_beams(dtype, D, R, k, L, W):
     check(dtype, D, R, k, L, W, "vectors", False, counts=(3, 512, None))
 

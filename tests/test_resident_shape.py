@@ -74,3 +74,10 @@ def test_uint8_kernels_of_long_frontiers_are_scheduled_for_four_waves(tmp_path):
           "ResidentLds<1, MetricU8<4, true, true>, VisitedLds16<12>, false>::kLaunchBytes == 0",
           *[f"ResidentLds<{k}, MetricU8Rows<1, true>, {small}, true>::kLaunchBytes == 0" for k in (1, 2, 4)],
           *[f"ResidentLds<{k}, MetricF32Lines<1>, {small}, true>::kLaunchBytes == 0" for k in (1, 2, 4)])
+
+
+def test_a_team_is_as_wide_as_its_beam(tmp_path):
+    # rows of up to 256 ids: a list fits the narrowest team that a beam of one gets
+    holds(tmp_path, *[f"detail::team_width({ids}, {most}) == {min(t, most)}" for most in (4, 8)
+                      for ids, t in ((1, 2), (64, 2), (128, 2), (129, 4), (256, 4), (257, most), (65536, most))],
+          "MetricU8<4, true, true>::team_waves(1) == 4", "MetricU8<4, true, true>::team_waves(4) == 8")
