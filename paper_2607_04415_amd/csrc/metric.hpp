@@ -490,10 +490,15 @@ struct MetricF32Lines {
   // evaluations are repeats.  100k nodes, 5,000 queries, L=200, us a call with
   // 32 KB and one wave / 16 KB and two: 20 floats, R=16 1,292 / 867, R=64 W=8
   // 2,036 / 1,393 (repeats 1% / 21%); 64 floats 1,497 / 957, 2,647 / 1,977.
-  // A batch that leaves one wave per SIMD anyway has the larger table
-  // (few_ht_log2; 200k x 32, R=64, W=8, L=200, 1,024 queries 548 / 632).
+  // A batch that leaves one wave per SIMD anyway has the larger table and, for
+  // three and four lines at any frontier, with it the room and the two batches
+  // of a kernel for one wave (few_ht_log2; us a call with the full batch's
+  // kernel / this one: 200k x 32, R=64, W=8, L=200, 1,024 queries 632 / 548;
+  // 200k x 96, R=64, W=8, L=64, 700 queries 295 / 249, 90 floats 329 / 275).
   __host__ __device__ static constexpr int ht_log2(int kpl) { return J <= 2 || (J <= 4 && kpl == 1) ? 13 : 14; }
-  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return kpl > 1 ? 14 : ht_log2(kpl); }
+  __host__ __device__ static constexpr int few_ht_log2(int kpl) {
+    return kpl > 1 || J == 3 || J == 4 ? 14 : ht_log2(kpl);
+  }
   __host__ __device__ static constexpr int waves_per_simd(int, uint32_t table_words) {
     return J <= 4 && table_words <= 4096 ? 2 : 1;
   }
@@ -685,7 +690,7 @@ struct MetricF32Own {
   static constexpr uint32_t kPadDist = 0x7F800000u;  // +inf
   // two waves and 16 KB, as MetricF32Lines of one line
   __host__ __device__ static constexpr int ht_log2(int) { return 13; }
-  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return ht_log2(kpl); }
+  __host__ __device__ static constexpr int few_ht_log2(int kpl) { return kpl > 1 ? 14 : ht_log2(kpl); }
   __host__ __device__ static constexpr int waves_per_simd(int, uint32_t table_words) { return table_words > 4096 ? 1 : 2; }
   __host__ __device__ static constexpr int grid_waves_per_simd(int kpl, uint32_t w) { return waves_per_simd(kpl, w); }
   __host__ __device__ static constexpr bool roomy(int, uint32_t) { return false; }

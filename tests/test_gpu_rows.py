@@ -70,13 +70,13 @@ def test_beams(dtype, D, R, k, L, W):
     check(dtype, D, R, k, L, W, "vectors", False, counts=(3, 512, None))
 
 
-# a wave per query with two and four frontier registers: beams of two groups,
+# a wave per query with each number of frontier registers: beams of two groups,
 # groups of up to four batches of 64, placed and not
 @pytest.mark.parametrize("layout,placed", [("vectors", False), ("vectors", True), ("contiguous", True)])
-@pytest.mark.parametrize("L", [100, 200])
+@pytest.mark.parametrize("L", [64, 100, 200])
 @pytest.mark.parametrize("dtype,D", [("u8", 16), ("u8", 64), ("u8", 128), ("u8", 200), ("u8", 300), ("f32", 5),
                                      ("f32", 20), ("f32", 32), ("f32", 64), ("f32", 90), ("f32", 96), ("f32", 128),
                                      ("f32", 150), ("f32", 256)])
-def test_long_frontiers(dtype, D, L, layout, placed):
+def test_wave_per_query(dtype, D, L, layout, placed):
     # 1,000: past the teams of eight, at most one wave per SIMD
     check(dtype, D, 64, 50, L, 8, layout, placed, counts=(1000, None))

@@ -57,6 +57,13 @@ def test_short_float32_rows_keep_two_waves_at_any_frontier(tmp_path):
           *[f"waves<{k}, MetricF32Lines<{J}>>() == 1" for J in (3, 4, 8) for k in (2, 4)])
 
 
+def test_a_batch_of_one_wave_per_simd_has_the_kernel_for_one(tmp_path):
+    few = "VisitedLds16<MetricF32Lines<{J}, true>::few_ht_log2({k})>::kWords"
+    holds(tmp_path, *[f"MetricF32Lines<{J}, true>::roomy({k}, {few.format(J=J, k=k)})" for J in (3, 4) for k in (1, 2, 4)],
+          *[f"MetricF32Lines<3, true>::two_batches({k}, {few.format(J=3, k=k)})" for k in (1, 2)],
+          "MetricF32Own::few_ht_log2(2) == 14")
+
+
 def test_whole_lines_have_two_batches_in_flight_with_either_table(tmp_path):
     large = "ResidentHtLarge::kWords"
     holds(tmp_path, *[f"MetricF32Lines<3, true>::two_batches({k}, {large})" for k in (1, 2)],
