@@ -162,20 +162,19 @@ __device__ __forceinline__ void eval_lines2(const M &m, const ResidentParams &p,
   if constexpr (NCH > 3) merge(3, m.template dist<ROOMY>(B));
 }
 
-template <int KPL, class M, uint32_t TABLE_WORDS, class Cands>
+template <int KPL, class M, bool TWO, bool ROOMY, class Cands>
 __device__ __forceinline__ void eval_group(const M &m, const ResidentParams &p, Cands &c, uint32_t cnt,
                                            uint64_t (&F)[KPL], bool forgot) {
-  constexpr bool kRoomy = M::roomy(KPL, TABLE_WORDS);
-  if constexpr (M::two_batches(KPL, TABLE_WORDS)) {
+  if constexpr (TWO) {
     switch ((cnt + kWave - 1) / kWave) {
-      case 1: eval_lines2<1, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
-      case 2: eval_lines2<2, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
-      case 3: eval_lines2<3, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
-      case 4: eval_lines2<4, KPL, M, kRoomy>(m, p, c, cnt, F, forgot); break;
+      case 1: eval_lines2<1, KPL, M, ROOMY>(m, p, c, cnt, F, forgot); break;
+      case 2: eval_lines2<2, KPL, M, ROOMY>(m, p, c, cnt, F, forgot); break;
+      case 3: eval_lines2<3, KPL, M, ROOMY>(m, p, c, cnt, F, forgot); break;
+      case 4: eval_lines2<4, KPL, M, ROOMY>(m, p, c, cnt, F, forgot); break;
       default: break;
     }
   } else if (cnt != 0) {
-    eval_lines<KPL, M, kRoomy>(m, p, c, cnt, F, forgot);
+    eval_lines<KPL, M, ROOMY>(m, p, c, cnt, F, forgot);
   }
 }
 
@@ -299,8 +298,13 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL, HT::kWords)) void sea
       // next group's lists while this group is filtered and evaluated, so only
       // the first group's round trip is exposed.  Other metrics read a group's
       // lists when they reach it: a uint8 beam at W=4 fits one group, and a
-      // second set of list registers would only constrain the allocator.
-      constexpr bool kAhead = M::kGathered;
+      // second set of list registers would only constrain the allocator.  So do
+      // rows with a placement, whose slot lookups between lists and gather wait
+      // for every load before them, the next group's lists too; for the same
+      // reason they keep one batch in flight (96 floats, placed, 5,000 queries,
+      // L=128, W=8, us a call with both / without: 6k nodes, R=32 864 / 773; 600k
+      // nodes 1,393 / 1,302).
+      constexpr bool kAhead = M::kGathered && !N2S;
       struct AdjLoad {
         uint64_t off;  // lane b: adjacency block of the group's beam b
         uint32_t deg;  // lane b: its degree
@@ -403,14 +407,15 @@ __global__ __launch_bounds__(kWave, M::waves_per_simd(KPL, HT::kWords)) void sea
             default: break;
           }
         } else if constexpr (M::kGathered) {
+          constexpr bool kTwo = !N2S && M::two_batches(KPL, HT::kWords), kRoomy = M::roomy(KPL, HT::kWords);
           if constexpr (Lds::kInStage) {
             LaneCandidates<N2S> c;
             c.read(cand, cand_slot, cnt, p.entry, entry_slot);
             asm volatile("" ::: "memory");  // read before the stage is written (LDS operations of one wave are in order)
-            eval_group<KPL, M, HT::kWords>(m, p, c, cnt, F, forgot);
+            eval_group<KPL, M, kTwo, kRoomy>(m, p, c, cnt, F, forgot);
           } else {
             LdsCandidates<N2S> c{cand, coff, cnt, p.entry, entry_off};
-            eval_group<KPL, M, HT::kWords>(m, p, c, cnt, F, forgot);
+            eval_group<KPL, M, kTwo, kRoomy>(m, p, c, cnt, F, forgot);
           }
         } else {
           // batches of kBatch vectors, one round trip each
