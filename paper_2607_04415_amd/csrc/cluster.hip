@@ -89,15 +89,25 @@ hipError_t assign(const T *v, uint64_t n, uint32_t D, uint32_t K, const ClusterW
   return hipGetLastError();
 }
 
-template <typename T>
-void launch_sums(const T *v, uint64_t n, uint32_t D, uint32_t K, const uint32_t *order, const uint32_t *start,
-                 double *sums, hipStream_t s) {
-  const dim3 grid(K, kMeanRanges);
-  auto threads = [](uint32_t units) { return std::min(256u, (units + 63) / 64 * 64); };
-  if (sizeof(T) == 1 && D % 4 == 0)
-    cluster_sums<T, sizeof(T) == 1 ? 4 : 1><<<grid, threads(D / 4), 0, s>>>(v, n, D, order, start, sums);
-  else
-    cluster_sums<T, 1><<<grid, threads(D), 0, s>>>(v, n, D, order, start, sums);
+// w.c = means of the clusters' members.  uint8: sums of K x D whole numbers;
+// float32: kMeanRanges x K x D float64.
+void update_means(const uint8_t *v, uint64_t n, uint32_t D, uint32_t K, const ClusterWork &w, const uint32_t *order,
+                  const uint32_t *start, void *sums, hipStream_t s) {
+  auto *whole = static_cast<unsigned long long *>(sums);
+  const uint64_t cells = (uint64_t)K * D;
+  fill_words<<<(unsigned)std::min<uint64_t>(4096, (2 * cells + 255) / 256), 256, 0, s>>>(
+      static_cast<uint32_t *>(sums), 2 * cells, 0u);
+  const unsigned grid = (unsigned)((n + kSumRows8 - 1) / kSumRows8);
+  if (D % 4 == 0) cluster_sums_u8<4><<<grid, 256, 0, s>>>(v, (uint32_t)n, D, order, w.key, start, whole);
+  else cluster_sums_u8<1><<<grid, 256, 0, s>>>(v, (uint32_t)n, D, order, w.key, start, whole);
+  cluster_means_u8<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(whole, start, K, D, w.c);
+}
+void update_means(const float *v, uint64_t n, uint32_t D, uint32_t K, const ClusterWork &w, const uint32_t *order,
+                  const uint32_t *start, void *sums, hipStream_t s) {
+  const uint64_t cells = (uint64_t)K * D;
+  cluster_sums_f32<<<kMeanRanges * K, std::min(256u, (D + 63) / 64 * 64), 0, s>>>(v, n, D, order, start,
+                                                                                 static_cast<double *>(sums));
+  cluster_means_f32<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(static_cast<double *>(sums), start, K, D, w.c);
 }
 
 }  // namespace
@@ -178,7 +188,7 @@ extern "C" gorio_status gorio_cluster_order(gorio_dtype dtype, const void *vecto
                o_key = take(n * 4), o_alt = take(n * 4), o_pairs = take(n * 4), o_open = take(n * 4),
                o_slot = take(n * 4), o_hist = take((size_t)tiles * K * 4), o_total = take((size_t)K * 4),
                o_start = take((size_t)(K + 1) * 4),
-               o_sums = take(iterations ? (size_t)kMeanRanges * K * D * sizeof(double) : 0);
+               o_sums = take(iterations ? (dtype == GORIO_U8 ? 1 : kMeanRanges) * (size_t)K * D * 8 : 0);
   Buf work;
   HIP_OR_FAIL(work.alloc(bytes));
   uint8_t *base = static_cast<uint8_t *>(work.p);
@@ -195,7 +205,6 @@ extern "C" gorio_status gorio_cluster_order(gorio_dtype dtype, const void *vecto
   w.open = words(o_open);
   uint32_t *slot = words(o_slot), *order = w.alt, *rank = w.pairs;  // the lists are done with by then
   uint32_t *hist = words(o_hist), *total = words(o_total), *start = words(o_start);
-  double *sums = reinterpret_cast<double *>(base + o_sums);
   const uint8_t *v8 = base + o_v;
   const float *vf = floats(o_v);
   HIP_OR_FAIL(hipMemcpyAsync(base + o_v, vectors, n * D * eb, hipMemcpyHostToDevice, s));
@@ -224,9 +233,8 @@ extern "C" gorio_status gorio_cluster_order(gorio_dtype dtype, const void *vecto
     if (it == iterations) break;
     // each centroid becomes the mean of its members (an empty cluster keeps
     // its centroid)
-    if (dtype == GORIO_U8) launch_sums(v8, n, D, K, order, start, sums, s);
-    else launch_sums(vf, n, D, K, order, start, sums, s);
-    cluster_means<<<(unsigned)(((uint64_t)K * D + 255) / 256), 256, 0, s>>>(sums, start, K, D, w.c);
+    if (dtype == GORIO_U8) update_means(v8, n, D, K, w, order, start, base + o_sums, s);
+    else update_means(vf, n, D, K, w, order, start, base + o_sums, s);
     HIP_OR_FAIL(hipGetLastError());
   }
   HIP_OR_FAIL(hipMemcpyAsync(c.data(), w.c, c.size() * 4, hipMemcpyDeviceToHost, s));

@@ -449,16 +449,61 @@ __global__ __launch_bounds__(256) void cluster_slots(const uint32_t *key, const 
 // ---------------------------------------------------------------------------
 // centroid means
 // ---------------------------------------------------------------------------
-// Sums in float64 in a stated order: the nodes in kMeanRanges ranges, each
-// range's members of a cluster in id order, then the ranges' sums in range
-// order.  Block (k, t): the members of cluster k in range t, one thread per V
-// consecutive dimensions, eight rows' loads in flight.
+// uint8: the sums are whole numbers below 2^53, the same in any order.  A block
+// takes kSumRows8 places of the order, whatever clusters they belong to: a
+// group of threads per row, V consecutive dimensions each, added up in LDS
+// and then once per cluster in memory.  So a cluster that holds most nodes is
+// shared among as many blocks as its rows need (1M x 128, all in one of 512
+// clusters, four iterations: 92.9 ms a call with 16 blocks to a cluster, 39.6
+// here; in one of one 25.2 and 6.4).
+constexpr uint32_t kSumRows8 = 1024;
+template <int V>
+__global__ __launch_bounds__(256) void cluster_sums_u8(const uint8_t *v, uint32_t n, uint32_t D, const uint32_t *order,
+                                                       const uint32_t *key, const uint32_t *start,
+                                                       unsigned long long *sums) {
+  __shared__ uint32_t part[1024];  // D <= 1024
+  struct __align__(V) Unit { uint8_t e[V]; };
+  const uint32_t units = D / V, groups = max(1u, blockDim.x / units);
+  const uint32_t g = units < blockDim.x ? threadIdx.x / units : 0u, u0 = threadIdx.x - g * units;
+  uint32_t p = blockIdx.x * kSumRows8;
+  const uint32_t last = min(n, p + kSumRows8);
+  while (p < last) {
+    const uint32_t k = key[order[p]], p1 = min(last, start[k + 1]);
+    for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) part[d] = 0;
+    __syncthreads();
+    if (g < groups) {
+      for (uint32_t u = u0; u < units; u += blockDim.x) {
+        uint32_t s[V] = {};
+#pragma unroll 8
+        for (uint32_t i = p + g; i < p1; i += groups) {
+          const Unit x = *reinterpret_cast<const Unit *>(v + (uint64_t)order[i] * D + u * V);
+#pragma unroll
+          for (int j = 0; j < V; ++j) s[j] += x.e[j];
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) atomicAdd(&part[u * V + j], s[j]);
+      }
+    }
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < D; d += blockDim.x)
+      if (part[d]) atomicAdd(&sums[(uint64_t)k * D + d], (unsigned long long)part[d]);
+    __syncthreads();
+    p = max(p + 1, p1);
+  }
+}
+
+// float32: sums in float64 in a stated order: the nodes in kMeanRanges ranges,
+// each range's members of a cluster in id order, then the ranges' sums in range
+// order.  Block 16 k + t: the members of cluster k in range t, one thread per
+// dimension; kFly rows are in flight while the kFly before them are added, and
+// their ids a step earlier, so that a cluster that holds most nodes costs one
+// memory trip per kFly rows (500k x 96, all in one of 256 clusters, four
+// iterations: 34.3 ms a call with 8 rows loaded and then added, 20.5 here).
 constexpr uint32_t kMeanRanges = 16;
 
-template <typename T, int V>
-__global__ __launch_bounds__(256) void cluster_sums(const T *v, uint64_t n, uint32_t D, const uint32_t *order,
-                                                    const uint32_t *start, double *sums) {
-  const uint32_t k = blockIdx.x, t = blockIdx.y, K = gridDim.x;
+__global__ __launch_bounds__(256) void cluster_sums_f32(const float *v, uint64_t n, uint32_t D, const uint32_t *order,
+                                                        const uint32_t *start, double *sums) {
+  const uint32_t t = blockIdx.x % kMeanRanges, k = blockIdx.x / kMeanRanges, K = gridDim.x / kMeanRanges;
   const uint32_t first = (uint32_t)(n * t / kMeanRanges), last = (uint32_t)(n * (t + 1) / kMeanRanges);
   auto lower = [&](uint32_t id) {  // first member of the cluster at or past id
     uint32_t a = start[k], b = start[k + 1];
@@ -467,40 +512,58 @@ __global__ __launch_bounds__(256) void cluster_sums(const T *v, uint64_t n, uint
       if (order[m] < id) a = m + 1;
       else b = m;
     }
-    return a;
+    return first_lane_value(a);
   };
   const uint32_t p0 = lower(first), p1 = lower(last);
-  struct __align__(sizeof(T) * V) Unit { T e[V]; };
-  constexpr int kFly = 8;
-  for (uint32_t u = threadIdx.x; u < D / V; u += blockDim.x) {
-    double s[V];
+  constexpr int kFly = 32;
+  for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) {
+    double s = 0.0;
+    if (p0 < p1) {
+      uint32_t id[kFly];
+      float now[kFly], next[kFly];
+      auto ids = [&](uint32_t p) {  // past the members: the last one again
 #pragma unroll
-    for (int j = 0; j < V; ++j) s[j] = 0.0;
-    uint32_t p = p0;
-    for (; p + kFly <= p1; p += kFly) {
-      Unit x[kFly];
+        for (int f = 0; f < kFly; ++f) id[f] = order[min(p + f, p1 - 1)];
+      };
+      auto rows = [&](float (&x)[kFly]) {
 #pragma unroll
-      for (int f = 0; f < kFly; ++f)
-        x[f] = *reinterpret_cast<const Unit *>(v + (uint64_t)order[p + f] * D + u * V);
+        for (int f = 0; f < kFly; ++f) x[f] = v[(uint64_t)id[f] * D + d];
+      };
+      ids(p0);
+      rows(now);
+      ids(p0 + kFly);
+      for (uint32_t p = p0; p < p1; p += kFly) {
+        if (p + kFly < p1) rows(next);
+        if (p + 2 * kFly < p1) ids(p + 2 * kFly);
+        const uint32_t m = min((uint32_t)kFly, p1 - p);
+        if (m == kFly) {
 #pragma unroll
-      for (int f = 0; f < kFly; ++f)
+          for (int f = 0; f < kFly; ++f) s = __dadd_rn(s, (double)now[f]);
+        } else {
 #pragma unroll
-        for (int j = 0; j < V; ++j) s[j] = __dadd_rn(s[j], (double)x[f].e[j]);
+          for (int f = 0; f < kFly; ++f)
+            if ((uint32_t)f < m) s = __dadd_rn(s, (double)now[f]);
+        }
+#pragma unroll
+        for (int f = 0; f < kFly; ++f) now[f] = next[f];
+      }
     }
-    for (; p < p1; ++p) {
-      const Unit x = *reinterpret_cast<const Unit *>(v + (uint64_t)order[p] * D + u * V);
-#pragma unroll
-      for (int j = 0; j < V; ++j) s[j] = __dadd_rn(s[j], (double)x.e[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < V; ++j) sums[((uint64_t)t * K + k) * D + u * V + j] = s[j];
+    sums[((uint64_t)t * K + k) * D + d] = s;
   }
 }
 
 // Each centroid becomes the mean of its members (an empty cluster keeps its
 // centroid).
-__global__ __launch_bounds__(256) void cluster_means(const double *sums, const uint32_t *start, uint32_t K, uint32_t D,
-                                                     float *c) {
+__global__ __launch_bounds__(256) void cluster_means_u8(const unsigned long long *sums, const uint32_t *start,
+                                                        uint32_t K, uint32_t D, float *c) {
+  const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= (uint64_t)K * D) return;
+  const uint32_t k = (uint32_t)(e / D);
+  const uint32_t cnt = start[k + 1] - start[k];
+  if (cnt != 0) c[e] = (float)__ddiv_rn((double)sums[e], (double)cnt);
+}
+__global__ __launch_bounds__(256) void cluster_means_f32(const double *sums, const uint32_t *start, uint32_t K,
+                                                         uint32_t D, float *c) {
   const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (uint64_t)K * D) return;
   const uint32_t k = (uint32_t)(e / D);

@@ -46,12 +46,19 @@ def plain(x, K, iterations):
 def data(kind, n, D, seed):
     rng = np.random.default_rng(seed)
     lab = rng.integers(0, 12, n)
+    if kind in ("same", "skew8"):   # all, or nearly all, rows the same: one cluster holds them
+        x = rng.integers(0, 256, (n, D)).astype(np.uint8)
+        x[rng.random(n) < (2.0 if kind == "same" else 0.97)] = x[0]
+        return x
     if kind == "u8":
         return np.clip(np.rint(rng.uniform(40, 215, (12, D))[lab] + 20 * rng.standard_normal((n, D))), 0, 255).astype(np.uint8)
     if kind == "equal":      # few distinct rows: most scores tie exactly
         return rng.integers(0, 3, (7, D)).astype(np.uint8)[rng.integers(0, 7, n)]
     x = (rng.standard_normal((12, D))[lab] + 0.05 * rng.standard_normal((n, D))).astype(np.float32)
-    if kind == "far":        # a large common offset: every score within rounding of the others
+    if kind == "skew":       # one cluster holds nearly all rows
+        x[rng.random(n) < 0.97] = x[0] + np.float32(0.25)
+        x[::2] += np.float32(1e-3) * rng.standard_normal((len(x[::2]), D)).astype(np.float32)
+    elif kind == "far":      # a large common offset: every score within rounding of the others
         x += np.float32(3000)
     elif kind == "nan":
         x[5, 0] = np.nan     # a row that is no initial centroid
@@ -70,6 +77,14 @@ def data(kind, n, D, seed):
     ("f32", 16400, 256, 48, 1),
     ("f32", 16400, 257, 32, 1),      # past the matrix path's dimensions
     ("equal", 16390, 64, 50, 2),
+    ("same", 16390, 128, 40, 2),     # every centroid repeats the first
+    ("skew8", 20000, 100, 33, 2),
+    ("skew8", 5001, 6, 9, 2),
+    ("skew8", 1500, 1023, 3, 1),     # a row over more threads than a block has
+    ("u8", 1025, 1024, 4, 1),        # one row past a block's share
+    ("skew", 17000, 96, 33, 2),      # ranges of a thousand members, no multiple of the rows in flight
+    ("skew", 40000, 300, 5, 2),
+    ("f32", 513, 70, 16, 2),         # ranges of no, one or two members
     ("far", 16390, 96, 40, 1),
     ("nan", 16390, 96, 40, 0),
     ("f32", 3, 5, 3, 1),
