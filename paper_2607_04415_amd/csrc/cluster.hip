@@ -53,6 +53,7 @@ struct ClusterWork {
   uint32_t Kp, DP;         // centroids and dimensions, padded for the matrix path
   float *c;                // K x D
   float *rows, *cols, *cc; // centroid_layouts' outputs
+  uint64_t *hash;
   unsigned int *flags;     // [pairs, open vectors, largest norm's bits]
   uint32_t *key, *alt, *pairs, *open;
 };
@@ -74,8 +75,10 @@ void launch_matrix(const T *v, uint64_t n, uint32_t D, const ClusterWork &w, hip
 template <typename T>
 hipError_t assign(const T *v, uint64_t n, uint32_t D, uint32_t K, const ClusterWork &w, hipStream_t s) {
   fill_words<<<1, 64, 0, s>>>(w.flags, 4, 0u);
-  centroid_layouts<<<(w.Kp + 63) / 64, 64, 0, s>>>(w.c, K, D, w.DP, w.Kp, w.rows, w.cols, w.cc, w.flags + 2);
+  centroid_layouts<<<(w.Kp + 63) / 64, 64, 0, s>>>(w.c, K, D, w.DP, w.Kp, w.rows, w.cols, w.cc, w.hash,
+                                                  w.flags + 2);
   if (!matrix_path(n, D, K)) return launch_nearest_centroid_t(v, n, D, w.c, w.cc, K, w.key, s);
+  drop_repeats<<<K, kWave, 0, s>>>(w.c, D, w.hash, w.cc);
   switch (w.DP) {
     case 32: launch_matrix<T, 4, 2>(v, n, D, w, s); break;
     case 64: launch_matrix<T, 8, 2>(v, n, D, w, s); break;
@@ -97,9 +100,10 @@ void update_means(const uint8_t *v, uint64_t n, uint32_t D, uint32_t K, const Cl
   const uint64_t cells = (uint64_t)K * D;
   fill_words<<<(unsigned)std::min<uint64_t>(4096, (2 * cells + 255) / 256), 256, 0, s>>>(
       static_cast<uint32_t *>(sums), 2 * cells, 0u);
-  const unsigned grid = (unsigned)((n + kSumRows8 - 1) / kSumRows8);
-  if (D % 4 == 0) cluster_sums_u8<4><<<grid, 256, 0, s>>>(v, (uint32_t)n, D, order, w.key, start, whole);
-  else cluster_sums_u8<1><<<grid, 256, 0, s>>>(v, (uint32_t)n, D, order, w.key, start, whole);
+  const uint32_t rows = sum_rows_u8(n);
+  const unsigned grid = (unsigned)((n + rows - 1) / rows);
+  if (D % 4 == 0) cluster_sums_u8<4><<<grid, 256, 0, s>>>(v, (uint32_t)n, D, rows, order, w.key, start, whole);
+  else cluster_sums_u8<1><<<grid, 256, 0, s>>>(v, (uint32_t)n, D, rows, order, w.key, start, whole);
   cluster_means_u8<<<(unsigned)((cells + 255) / 256), 256, 0, s>>>(whole, start, K, D, w.c);
 }
 void update_means(const float *v, uint64_t n, uint32_t D, uint32_t K, const ClusterWork &w, const uint32_t *order,
@@ -184,7 +188,8 @@ extern "C" gorio_status gorio_cluster_order(gorio_dtype dtype, const void *vecto
     return at;
   };
   const size_t o_v = take(n * D * eb), o_c = take((size_t)K * D * 4), o_rows = take((size_t)w.Kp * w.DP * 4),
-               o_cols = take((size_t)w.Kp * D * 4), o_cc = take((size_t)w.Kp * 4), o_flags = take(16),
+               o_cols = take((size_t)w.Kp * D * 4), o_cc = take((size_t)w.Kp * 4), o_hash = take((size_t)w.Kp * 8),
+               o_flags = take(16),
                o_key = take(n * 4), o_alt = take(n * 4), o_pairs = take(n * 4), o_open = take(n * 4),
                o_slot = take(n * 4), o_hist = take((size_t)tiles * K * 4), o_total = take((size_t)K * 4),
                o_start = take((size_t)(K + 1) * 4),
@@ -198,6 +203,7 @@ extern "C" gorio_status gorio_cluster_order(gorio_dtype dtype, const void *vecto
   w.rows = floats(o_rows);
   w.cols = floats(o_cols);
   w.cc = floats(o_cc);
+  w.hash = reinterpret_cast<uint64_t *>(base + o_hash);
   w.flags = words(o_flags);
   w.key = words(o_key);
   w.alt = words(o_alt);

@@ -2,6 +2,8 @@
 // units, a stable counting sort by cluster, and the centroid means.
 #pragma once
 
+#include <algorithm>
+
 #include "wave.hpp"
 
 namespace gorio {
@@ -61,12 +63,15 @@ __global__ __launch_bounds__(256) void nearest_centroid(const T *v, uint64_t cou
 // Centroids laid out for the matrix path: rows of DP floats (zeros past D),
 // a whole number of 32-row tiles; scores of the padding rows are +inf.  Also
 // the transposed rows (Kp floats per dimension), the squared norms in d order,
-// and the largest norm's bits (a NaN's compare above every number's).
+// a hash of each centroid's bits, and the largest norm's bits (a NaN's compare
+// above every number's).
 __global__ __launch_bounds__(64) void centroid_layouts(const float *c, uint32_t K, uint32_t D, uint32_t DP, uint32_t Kp,
-                                                       float *rows, float *cols, float *cc, unsigned int *most) {
+                                                       float *rows, float *cols, float *cc, uint64_t *hash,
+                                                       unsigned int *most) {
   const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= Kp) return;
   float s = 0.0f;
+  uint64_t h = 0;
 #pragma unroll 8
   for (uint32_t d = 0; d < DP; ++d) {
     const float x = k < K && d < D ? c[(uint64_t)k * D + d] : 0.0f;
@@ -74,10 +79,34 @@ __global__ __launch_bounds__(64) void centroid_layouts(const float *c, uint32_t 
     if (d < D) {
       cols[(uint64_t)d * Kp + k] = x;
       s = __fadd_rn(s, __fmul_rn(x, x));
+      h = (h ^ __float_as_uint(x)) * 0x9E3779B97F4A7C15ull;
+      h ^= h >> 29;
     }
   }
+  hash[k] = h;
   cc[k] = k < K ? s : __uint_as_float(0x7F800000u);
   if (k < K) atomicMax(most, __float_as_uint(s) & 0x7FFFFFFFu);
+}
+
+// A centroid with the bits of an earlier one never wins (equal scores, larger
+// index), but its ties would send every vector near it to the exact scores: its
+// norm becomes +inf.  A wave per centroid looks for the first earlier one with
+// its hash and compares the two; a hash in common with a different centroid
+// leaves it as it is.  (1M x 128 uint8, all rows equal, 512 clusters, four
+// iterations: 39.6 ms a call without, 12.7 with.)
+__global__ __launch_bounds__(kWave) void drop_repeats(const float *c, uint32_t D, const uint64_t *hash, float *cc) {
+  const uint32_t k = blockIdx.x, l = lane_id();
+  const uint64_t h = hash[k];
+  for (uint32_t j0 = 0; j0 < k; j0 += kWave) {
+    const uint64_t m = ballot(j0 + l < k && hash[j0 + l] == h);
+    if (m == 0) continue;
+    const uint32_t j = j0 + (uint32_t)__builtin_ctzll(m);
+    bool same = true;
+    for (uint32_t d = l; d < D; d += kWave)
+      same = same && __float_as_uint(c[(uint64_t)j * D + d]) == __float_as_uint(c[(uint64_t)k * D + d]);
+    if (ballot(!same) == 0 && l == 0) cc[k] = __uint_as_float(0x7F800000u);
+    return;
+  }
 }
 
 // How far two computations of one score may lie apart on either side, twice:
@@ -450,23 +479,26 @@ __global__ __launch_bounds__(256) void cluster_slots(const uint32_t *key, const 
 // centroid means
 // ---------------------------------------------------------------------------
 // uint8: the sums are whole numbers below 2^53, the same in any order.  A block
-// takes kSumRows8 places of the order, whatever clusters they belong to: a
+// takes `rows` places of the order, whatever clusters they belong to: a
 // group of threads per row, V consecutive dimensions each, added up in LDS
 // and then once per cluster in memory.  So a cluster that holds most nodes is
 // shared among as many blocks as its rows need (1M x 128, all in one of 512
 // clusters, four iterations: 92.9 ms a call with 16 blocks to a cluster, 39.6
 // here; in one of one 25.2 and 6.4).
-constexpr uint32_t kSumRows8 = 1024;
+// About a thousand blocks, of 64 rows at least (a cluster's share costs four
+// dependent loads; 20k nodes, 64 clusters, two iterations: 0.86 ms a call with
+// 1,024 rows to a block, 0.75 so).
+inline uint32_t sum_rows_u8(uint64_t n) { return (uint32_t)std::min<uint64_t>(1024, std::max<uint64_t>(64, n / 1024)); }
 template <int V>
-__global__ __launch_bounds__(256) void cluster_sums_u8(const uint8_t *v, uint32_t n, uint32_t D, const uint32_t *order,
-                                                       const uint32_t *key, const uint32_t *start,
-                                                       unsigned long long *sums) {
+__global__ __launch_bounds__(256) void cluster_sums_u8(const uint8_t *v, uint32_t n, uint32_t D, uint32_t rows,
+                                                       const uint32_t *order, const uint32_t *key,
+                                                       const uint32_t *start, unsigned long long *sums) {
   __shared__ uint32_t part[1024];  // D <= 1024
   struct __align__(V) Unit { uint8_t e[V]; };
   const uint32_t units = D / V, groups = max(1u, blockDim.x / units);
   const uint32_t g = units < blockDim.x ? threadIdx.x / units : 0u, u0 = threadIdx.x - g * units;
-  uint32_t p = blockIdx.x * kSumRows8;
-  const uint32_t last = min(n, p + kSumRows8);
+  uint32_t p = blockIdx.x * rows;
+  const uint32_t last = min(n, p + rows);
   while (p < last) {
     const uint32_t k = key[order[p]], p1 = min(last, start[k + 1]);
     for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) part[d] = 0;
