@@ -113,6 +113,9 @@ GORIO_HD bool run_stand_ins(double start, double lo, double hi, double margin, d
 // 2^e for e within the normal range.
 GORIO_HD double sum_pow2(int e) { return sum_bits_as_double((uint64_t)(e + 1023) << 52); }
 
+// The mark of an open run whose terms are added one after another.
+GORIO_HD double sum_open_mark() { return sum_bits_as_double(0x7FF8000000000000ull); }
+
 // The mark of an open run (see RunAmount): with far < 2^e the bound of its
 // partial sums, whole multiples of 2^(e - 52) are added without rounding.
 GORIO_HD RunAmount run_open(const RunOutline &o, double margin) {
@@ -122,7 +125,7 @@ GORIO_HD RunAmount run_open(const RunOutline &o, double margin) {
     const int unit = (int)(sum_double_bits(far) >> 52) - 1023 + 1 - 52;
     if (unit > -1000 && o.low >= unit) return {sum_bits_as_double(nan | (uint64_t)(unit + kUnitBias)), 0.0};
   }
-  return {sum_bits_as_double(nan), 0.0};
+  return {sum_open_mark(), 0.0};
 }
 // Whether an open run's plain sum can be added to s.
 GORIO_HD bool run_is_exact(double s, double mark) {

@@ -35,7 +35,8 @@ def test_runs_equal_the_plain_loop(harness, kind, n):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,D,kind", [(1, 1, "drift"), (256, 3, "walk"), (257, 96, "drift"), (20_000, 1, "drift"),
+@pytest.mark.parametrize("n,D,kind", [(1, 1, "drift"), (256, 3, "walk"), (257, 96, "drift"), (1024, 7, "walk"), (1025, 7, "walk"),
+                                      (20_000, 1, "drift"),
                                       (20_000, 1, "flip"), (30_001, 65, "walk"), (30_001, 1, "whole")])
 def test_entry_is_the_oracles(n, D, kind):
     import torch
