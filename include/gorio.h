@@ -334,6 +334,9 @@ gorio_status gorio_locality_order(const uint32_t *graph, uint64_t n, uint32_t R,
  *   node_to_slot: host out, n entries, a permutation of [0, n).
  *   centroids:  host out, K x D float32 (the final centroids).
  * Deterministic.  Results of a search never depend on the placement.
+ * Device memory during the call: the vectors, 20 bytes per node, at most 256 MB
+ * of counts, about 12 K D bytes of centroids and, with iterations, 8 K D (uint8)
+ * or 128 K D (float32) bytes of sums.
  * Errors: GORIO_EINVAL for NULL pointers or n, D (1..1024), K, iterations out of
  * range; GORIO_ENOMEM / GORIO_EDEVICE from the device.
  */

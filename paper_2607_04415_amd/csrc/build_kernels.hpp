@@ -184,18 +184,19 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 }
 
 // One wave per column: 64 runs' amounts are read at once, one per lane, and
-// added one after another; an open run's rows likewise.  Without amounts
-// (nullptr) every run is open.
+// added one after another; an open run's rows likewise.  Without AMOUNTS every
+// run is open.
+template <bool AMOUNTS>
 __global__ __launch_bounds__(kWave) void sum_chain_f32(const float *x, uint32_t n, uint32_t D, uint32_t runs,
                                                        const RunAmount *amounts, double *sums) {
   const uint32_t d = blockIdx.x, l = lane_id();
   double s = 0.0;
   RunAmount next = {sum_open_mark(), 0.0};
-  if (amounts && l < runs) next = amounts[(uint64_t)l * D + d];
+  if (AMOUNTS && l < runs) next = amounts[(uint64_t)l * D + d];
   for (uint32_t c0 = 0; c0 < runs; c0 += kWave) {
     const RunAmount a = next;
     const uint32_t cn = c0 + kWave + l;
-    if (amounts && cn < runs) next = amounts[(uint64_t)cn * D + d];
+    if (AMOUNTS && cn < runs) next = amounts[(uint64_t)cn * D + d];
     const uint64_t open = ballot(!(a.even == a.even));
     const uint32_t m = min((uint32_t)kWave, runs - c0);
     for (uint32_t j = 0; j < m; ++j) {

@@ -217,9 +217,10 @@ extern "C" gorio_status gorio_build_index(gorio_dtype dtype, const void *vectors
         sum_starts_f32<<<D, 256, 0, s>>>(outlines.as<RunOutline>(), plain, D, runs, most);
         sum_amounts_f32<<<grid, 256, 0, s>>>(x, (uint32_t)n, D, runs, outlines.as<RunOutline>(), plain, most,
                                              amounts.as<RunAmount>());
+        sum_chain_f32<true><<<D, kWave, 0, s>>>(x, (uint32_t)n, D, runs, amounts.as<RunAmount>(), sums.as<double>());
+      } else {
+        sum_chain_f32<false><<<D, kWave, 0, s>>>(x, (uint32_t)n, D, runs, nullptr, sums.as<double>());
       }
-      sum_chain_f32<<<D, kWave, 0, s>>>(x, (uint32_t)n, D, runs, runs > kSumDirectRuns ? amounts.as<RunAmount>() : nullptr,
-                                        sums.as<double>());
       nearest_to_centroid_f32<<<grid_for(n, 256, 2048), 256, 0, s>>>(d_vec.as<float>(), (uint32_t)n, D,
                                                                     sums.as<double>(), best);
     }

@@ -9,8 +9,9 @@
 //   select  - the first W unexpanded slots of F (ballot + prefix count);
 //   expand  - one round trip reads the degree and id list of every chosen
 //             node of a beam group (up to 256 ids, 4 per lane); with float32
-//             line-gathered rows a beam of several groups reads the next
-//             group's lists while the current one is filtered and evaluated;
+//             line-gathered rows (no placement) a beam of several groups reads
+//             the next group's lists while the current one is filtered and
+//             evaluated;
 //   filter  - ids already in the visited filter are dropped (LDS atomics),
 //             the rest compacted into an LDS candidate list;
 //   evaluate- one round trip gathers a batch of candidate vectors by whole

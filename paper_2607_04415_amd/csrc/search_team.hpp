@@ -19,8 +19,9 @@
 //   merge    every wave, all of those keys.
 // Bound by two dependent memory trips per iteration (lists, vectors; about 2.8
 // us an iteration with the barriers and LDS steps between them).  1M x 128
-// uint8, R=64, L=64, W=4: one query 109 -> 62 us a call, 1,024 queries 197 ->
-// 140; 200k x 96 float32, 32 queries 199 -> 124.  Touching the lists of all
+// uint8, R=64, L=64, W=4: one query, the same again 100 -> 64 us a call, another
+// each time 118 -> 78; 1,024 queries 197 -> 140; 200k x 96 float32, 32 queries
+// 199 -> 124.  Touching the lists of all
 // new candidates together with their vectors, so that the next beam's were in
 // the caches, made both slower (82 and 142 us).
 //
