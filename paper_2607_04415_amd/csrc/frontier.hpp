@@ -153,8 +153,11 @@ static __device__ __noinline__ FrontierRegs<KPL> sort_merge_call(FrontierRegs<KP
 // Merge one key per lane (kInfKey = none) into F: keys at or above F's L-th
 // key cannot enter; a few survivors are inserted by rank, more are sorted
 // and bitonic-merged (with dedupe once the visited filter has forgotten a
-// node).  Slots past L are cleared.
-template <int KPL, bool CALL = true>
+// node).  Slots past L are cleared.  IN_PLACE (inline only): sorted and merged
+// where F is, without the copies to and from FrontierRegs, which make the paged
+// kernels with two frontier registers 1 to 2% larger (60k x 96 float32, L=128,
+// 100 queries, cache 10%: 29.5 ms with them, 28.6 without).
+template <int KPL, bool CALL = true, bool IN_PLACE = false>
 __device__ __forceinline__ void merge_keys(uint64_t (&F)[KPL], uint64_t key, bool forgot, uint32_t L) {
   const uint64_t thr = frontier_at<KPL>(F, L - 1);
   const bool pass = key < thr;
@@ -166,6 +169,16 @@ __device__ __forceinline__ void merge_keys(uint64_t (&F)[KPL], uint64_t key, boo
       const int lane = __builtin_ctzll(pm);
       pm &= pm - 1;
       insert_key<KPL>(F, readlane64(key, lane));
+    }
+  } else if constexpr (IN_PLACE && !CALL) {
+    uint64_t cc[1] = {key};
+    bitonic_sort<1, true>(cc);
+    if (!forgot) {
+      // no node can repeat: the P smallest of F and C are min(F, C reversed)
+      F[KPL - 1] = min64(F[KPL - 1], cc[0]);
+      bitonic_merge_up<KPL>(F);
+    } else {
+      merge_dedupe<KPL>(F, cc[0]);
     }
   } else {
     FrontierRegs<KPL> x;

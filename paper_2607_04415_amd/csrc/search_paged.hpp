@@ -509,7 +509,7 @@ __device__ bool run_query(const PagedParams &p, QSlot<KPL> &S, uint32_t *ht, uin
           uint64_t key = m.paged_keys([&](uint32_t si, uint32_t v) { return cached_vec<N2S>(p, si, v); }, crs,
                                       S.cand, t * kWave, rdy[t], rslot[t], mr);
           ctr.eval += cnt;
-          merge_keys<KPL, KPL == 1>(F, key, S.forgot != 0, p.L);
+          merge_keys<KPL, KPL == 1, true>(F, key, S.forgot != 0, p.L);
           if (rdy[t]) {
             unpin(p.cache, rslot[t]);
             S.cstate[t * kWave + l] = kDone;
